@@ -4,6 +4,8 @@
 // so the neighbour set equals the brute-force definition bit for bit.
 #include <math.h>
 
+#include <algorithm>
+
 #include "md_internal.h"
 
 namespace {
@@ -270,14 +272,40 @@ __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bin_copyback(
 // ---------------------------------------------------------------------------
 // Verlet list (Sec. 1.4): the candidates of every atom of a cell are the atoms of
 // the (de-duplicated) 3x3x3 block of cells around it, the same set for all atoms
-// of the cell.  One wavefront takes one cell: its lanes hold 64 candidates at a
-// time (positions in registers, loaded once per cell rather than once per atom)
-// and test them against each atom of the cell in turn; a ballot of the accepted
-// lanes gives every accepted candidate its slot, so the list is written in
-// candidate order (stencil cell order, then cell order) in a single pass.
+// of the cell.  One block takes one cell: its four wavefronts stage the candidates in
+// LDS together and then take the cell's atoms four at a time.  Lists are written in
+// candidate order (stencil cell order, then cell order).
 // ---------------------------------------------------------------------------
-constexpr int CW = 4;                  // wavefronts (cells) per block
+constexpr int CW = 4;                  // wavefronts per block
 constexpr int CELL_BLOCK = CW * MD_WAVE;
+constexpr int SEG_MAX = 64;            // most candidates per four-lane segment (16 segments)
+constexpr int LSLOT = 130;             // list slots per atom in LDS (a stride of 65 banks)
+
+// LDS of a block besides the candidates.
+struct CellLds {
+  unsigned short list[CW][4 * LSLOT];      // the lists of a wavefront's four atoms, as candidates
+  int beg[33], start[32];                  // cell_lists: stencil ranges' first candidates, atoms
+  // found by the first wavefront: runs of stencil cells that follow one another in memory with
+  // one image (the z-neighbours where they do not wrap)
+  int n_runs, C, own, a0, na, img, fixed, rep;
+  int run_v[28], run_j[27];                // first candidate and first atom
+  double run_off[27][3];                   // L k + cell centre
+  double ctr[3], edge[3];                  // the cell's centre, 1.5 cell edges
+};
+// The candidates, in dynamic LDS for `seg` per segment: records {-2 u, |u|^2} by segment (rows
+// of 4 mod 8 records, so that 64 lanes' reads meet no bank twice), then their atoms.  The FP64
+// form keeps 64 positions per wavefront there.
+static inline size_t candidate_lds(int seg) {
+  return std::max<size_t>(16 * (seg + 4) * 16 + 16 * seg * 4, CW * 3 * MD_WAVE * sizeof(double));
+}
+
+using f32x4 = float __attribute__((ext_vector_type(4)));
+
+// LDS written by this wavefront's other lanes is read next.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // Stencil cell t (0..2) along one axis for an atom in cell c: the cell index, or -1
 // when there is none (outside a non-periodic box, or a duplicate when nc < 3), and
@@ -299,62 +327,59 @@ __device__ __forceinline__ int stencil_cell(int c, int t, int nc, int periodic, 
   return q;
 }
 
-// Test modes: PLAIN for a cell whose block does not wrap (d itself is the minimum
-// image: |d| < 2 w <= 2 L / 5 < L / 2 when nc >= 5), SHIFT for a wrapping block
-// with nc >= 5 on every periodic axis (the image of each stencil cell is fixed, so
-// d - L k is the minimum image, the same operations as d - L rint(d / L)), RINT
-// for small grids (nc < 5 on a periodic axis): the minimum image per candidate.
-enum { PLAIN = 0, SHIFT = 1, RINT = 2 };
-
 struct Cand {
   double x, y, z;     // candidate position
-  double sx, sy, sz;  // L k per axis (SHIFT)
   int j;              // candidate index
   bool valid;
 };
 
 // Entry `slot` of atom ia: row slot / lanes, column ia * lanes + slot % lanes.
-// FAST: the whole list spans < 4 GiB and a row < 2^24 ints, so a 32-bit byte offset
-// from the atom's (wave-uniform) first entry addresses it.
-template <bool FAST>
 __device__ __forceinline__ int* entry(int* neigh, int ia, int slot, int lanes_log2,
                                       unsigned row) {
-  const int lanes = 1 << lanes_log2;
-  int* at = neigh + (size_t)ia * lanes;
-  const unsigned q = (unsigned)slot >> lanes_log2, col = (unsigned)slot & (lanes - 1);
-  return FAST ? (int*)((char*)at + ((__umul24(q, row) + col) << 2)) : at + ((size_t)q * row + col);
+  const unsigned lanes = 1u << lanes_log2;
+  return neigh + (size_t)ia * lanes + (size_t)((unsigned)slot >> lanes_log2) * row +
+         ((unsigned)slot & (lanes - 1));
 }
 
-
-// Candidate c against atom k of the cell (position in s_p, index ia).
-template <int MODE>
+// Candidate c against atom k of the cell (position in s_p, index ia), with the minimum
+// image per candidate.
 __device__ __forceinline__ bool accept_pair(const Cand& c, double (*s_p)[MD_WAVE], int k, int ia,
                                             const double* len, const double* inv, const int* per,
                                             double rns2) {
   double dx = c.x - s_p[0][k], dy = c.y - s_p[1][k], dz = c.z - s_p[2][k];
-  if (MODE == SHIFT) {
-    dx = dx - c.sx;
-    dy = dy - c.sy;
-    dz = dz - c.sz;
-  } else if (MODE == RINT) {
-    if (per[0]) dx = dx - len[0] * rint(dx * inv[0]);
-    if (per[1]) dy = dy - len[1] * rint(dy * inv[1]);
-    if (per[2]) dz = dz - len[2] * rint(dz * inv[2]);
-  }
+  if (per[0]) dx = dx - len[0] * rint(dx * inv[0]);
+  if (per[1]) dy = dy - len[1] * rint(dy * inv[1]);
+  if (per[2]) dz = dz - len[2] * rint(dz * inv[2]);
   const double r2 = (dx * dx + dy * dy) + dz * dz;
   return c.valid & (c.j != ia) & (r2 < rns2);
 }
 
-template <int MODE, bool FAST>
+// Overflow flag and longest list of a wavefront's atoms.  The longest list is one word for all
+// wavefronts: only those that raise it touch it with an atomic (one atomicMax per wavefront, all
+// to one address, took 10 ns each one after the other and set the whole build's time: 118 us on
+// 131k Cu atoms whatever the rest of the kernel did).
+__device__ __forceinline__ void publish_counts(int over, int most, md_ctl_dev* ctl) {
+  const int lane = threadIdx.x & (MD_WAVE - 1);
+  if (__any(over)) {
+    if (lane == 0) md_flag(ctl, MD_FLAG_NEIGH_OVERFLOW);
+  }
+#pragma unroll
+  for (int o = MD_WAVE / 2; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, MD_WAVE));
+  if (lane == 0 &&
+      most > __hip_atomic_load(&ctl->max_nneigh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(&ctl->max_nneigh, most);
+}
+
+// The lists of a cell by FP64 tests: the general form, for grids whose cells hold several
+// images of a pair (two cells on a periodic axis) and for cells that k_build cannot stage.
 __device__ __forceinline__ void cell_lists(const md_domain& D, int a0, int na, int C,
                                            const int* s_beg, const int* s_start,
-                                           const int* s_code, double (*s_p)[MD_WAVE],
+                                           double (*s_p)[MD_WAVE],
                                            const double4* __restrict__ pos, int* neigh,
                                            int* nneigh, int max_neigh, int lanes_log2, int npad,
-                                           double rns2, bool img, md_ctl_dev* ctl) {
+                                           double rns2, bool img, int& over, int& most) {
   const int lane = threadIdx.x & (MD_WAVE - 1);
-  const int lanes = 1 << lanes_log2;
-  const unsigned row = (unsigned)npad * lanes;  // ints per list row
+  const unsigned row = (unsigned)npad << lanes_log2;  // ints per list row
   double len[3], inv[3];
   int per[3];
 #pragma unroll
@@ -376,14 +401,8 @@ __device__ __forceinline__ void cell_lists(const md_domain& D, int a0, int na, i
     c.x = q.x;
     c.y = q.y;
     c.z = q.z;
-    const int code = s_code[r];
-    const int kx = (code & 3) - 1, ky = ((code >> 2) & 3) - 1, kz = ((code >> 4) & 3) - 1;
-    c.sx = kx == 0 ? 0.0 : (kx > 0 ? len[0] : -len[0]);
-    c.sy = ky == 0 ? 0.0 : (ky > 0 ? len[1] : -len[1]);
-    c.sz = kz == 0 ? 0.0 : (kz > 0 ? len[2] : -len[2]);
     return c;
   };
-  int over = 0, most = 0;
   for (int g0 = 0; g0 < na; g0 += MD_WAVE) {
     const int gc = min(MD_WAVE, na - g0);
     if (lane < gc) {
@@ -401,8 +420,8 @@ __device__ __forceinline__ void cell_lists(const md_domain& D, int a0, int na, i
       // two atoms per trip: their distance chains overlap
       for (int k = 0; k < gc; k += 2) {
         const int k1 = min(k + 1, gc - 1);  // gc odd: the last trip tests atom k twice
-        const bool ok0 = accept_pair<MODE>(c, s_p, k, a0 + g0 + k, len, inv, per, rns2);
-        const bool ok1 = accept_pair<MODE>(c, s_p, k1, a0 + g0 + k1, len, inv, per, rns2) &&
+        const bool ok0 = accept_pair(c, s_p, k, a0 + g0 + k, len, inv, per, rns2);
+        const bool ok1 = accept_pair(c, s_p, k1, a0 + g0 + k1, len, inv, per, rns2) &&
                          k1 != k;
         const unsigned long long m0 = __builtin_amdgcn_ballot_w64(ok0);
         const unsigned long long m1 = __builtin_amdgcn_ballot_w64(ok1);
@@ -410,9 +429,9 @@ __device__ __forceinline__ void cell_lists(const md_domain& D, int a0, int na, i
         const int base1 = __builtin_amdgcn_readlane(tot, k1);
         const int slot0 = base0 + lanes_below(m0), slot1 = base1 + lanes_below(m1);
         if (ok0 && slot0 < max_neigh)
-          *entry<FAST>(neigh, a0 + g0 + k, slot0, lanes_log2, row) = c.j;
+          *entry(neigh, a0 + g0 + k, slot0, lanes_log2, row) = c.j;
         if (ok1 && slot1 < max_neigh)
-          *entry<FAST>(neigh, a0 + g0 + k1, slot1, lanes_log2, row) = c.j;
+          *entry(neigh, a0 + g0 + k1, slot1, lanes_log2, row) = c.j;
         tot = lane == k ? base0 + (int)__popcll(m0) : tot;
         tot = lane == k1 && k1 != k ? base1 + (int)__popcll(m1) : tot;
       }
@@ -424,93 +443,346 @@ __device__ __forceinline__ void cell_lists(const md_domain& D, int a0, int na, i
     }
     __builtin_amdgcn_wave_barrier();
   }
-  if (__any(over)) {
-    if (lane == 0) md_flag(ctl, MD_FLAG_NEIGH_OVERFLOW);
-  }
-#pragma unroll
-  for (int o = MD_WAVE / 2; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, MD_WAVE));
-  if (lane == 0 && most > 0) atomicMax(&ctl->max_nneigh, most);
 }
 
-__global__ __launch_bounds__(CELL_BLOCK) void k_build(md_batch b, int mode,
-                                                      const double4* __restrict__ pos,
-                                                      const int* __restrict__ cell_start,
-                                                      int* neigh, int* nneigh, int max_neigh,
-                                                      int lanes_log2, int npad, double rns2,
-                                                      md_ctl_dev* ctl) {
-  if (skip_rebuild(mode, ctl)) return;
-  __shared__ int s_beg[CW][33], s_start[CW][32], s_code[CW][32];
-  __shared__ double s_p[CW][3][MD_WAVE];
-  const int w = threadIdx.x / MD_WAVE, lane = threadIdx.x & (MD_WAVE - 1);
-  const int cell = md_remap_block((b.n_cells + CW - 1) / CW) * CW + w;
-  if (cell >= b.n_cells) return;  // whole wavefronts only
-  // the box of this cell: the last domain whose cells start at or before it
-  int lo = 0, hi = b.n_rep - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (b.domains[mid].cell_off <= cell) lo = mid; else hi = mid - 1;
-  }
-  const md_domain& D = b.domains[lo];
-  const int a0 = __builtin_amdgcn_readfirstlane(cell_start[cell]);
-  const int na = __builtin_amdgcn_readfirstlane(cell_start[cell + 1]) - a0;
-  if (na == 0) return;
-  const int local = cell - D.cell_off;
-  const int c2 = local % D.nc[2], c1 = (local / D.nc[2]) % D.nc[1], c0 = local / (D.nc[2] * D.nc[1]);
-  // lane t < 27 takes stencil cell (t / 9, t / 3 % 3, t % 3): its atom range and image
-  int cnt = 0, start = 0, code = 0;
-  if (lane < 27) {
-    int kx, ky, kz;
-    const int qx = stencil_cell(c0, lane / 9, D.nc[0], D.periodic[0], kx);
-    const int qy = stencil_cell(c1, (lane / 3) % 3, D.nc[1], D.periodic[1], ky);
-    const int qz = stencil_cell(c2, lane % 3, D.nc[2], D.periodic[2], kz);
-    if (qx >= 0 && qy >= 0 && qz >= 0) {
-      const int q = D.cell_off + (qx * D.nc[1] + qy) * D.nc[2] + qz;
-      start = cell_start[q];
-      cnt = cell_start[q + 1] - start;
-      code = (kx + 1) | ((ky + 1) << 2) | ((kz + 1) << 4);
-    }
-  }
-  // exclusive prefix of the range sizes over the lanes
-  int incl = cnt;
+// The value of a lane of the same group of four (CTRL: two bits per lane), and of the lane N
+// below in the same row of 16 (0 if there is none).
+template <int CTRL>
+__device__ __forceinline__ int quad_perm(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
+}
+template <int N>
+__device__ __forceinline__ int row_shr(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x110 + N, 0xF, 0xF, true);
+}
+
+// v / S for 0 <= v < 1024, 4 <= S <= 64 (the reciprocal is uniform).
+__device__ __forceinline__ int segment_of(int v, int S) {
+  return (int)((unsigned)v * (((1u << 20) + S - 1) / S) >> 20);
+}
+
+// The lists of four atoms of a cell by matrix instructions: squared distances
+//   r_ij^2 - r_ns^2 = (|u_i|^2 - r_ns^2) + |u_j|^2 - 2 u_i . u_j
+// (u relative to the cell's centre) of four candidates {-2 u_j, |u_j|^2} and the four atoms
+// {u_i, 1} come from four v_mfma_f32_4x4x1 (16 such blocks at once), and the sign of each
+// element decides its pair.  Lane 4 b + i takes atom i and the b-th of 16 equal segments of the
+// candidates: it shifts the four signs it gets per step into bit masks and then lists its
+// segment's accepted candidates one by one, its first slot being the number accepted in the
+// segments below: candidate order, as from cell_lists.  The four lists are put together in LDS
+// and written row by row.
+//
+// The decisions are those of the FP64 test, bit for bit.  With A = max |u_i|, a pair with
+// |u_j| <= A + 1.05 r_ns is formed with an error of at most tau = 2^-20 ((2 A + 1.05 r_ns)^2 +
+// r_ns^2) (inputs, norms and four accumulations, each within 2 x 2^-24 of the sum of
+// magnitudes), and one farther out has r^2 - r_ns^2 > 0.09 r_ns^2, far more than its error.  If
+// any element is within tau of zero (about 1 % of the four-atom groups of a thermal crystal),
+// the group's accepted candidates, with tau added to r_ns^2, are tested again in FP64
+// (accept_pair's operations: d - L k with the image k of the candidate's stencil cell).
+__device__ __forceinline__ void atom_lists(const md_domain& D, int a0, int na, int t, int S, int own, CellLds& s,
+                                           const float (*recs)[4], const int* cand, int w,
+                                           const double4* __restrict__ pos, int* neigh,
+                                           int* nneigh, int max_neigh, int lanes_log2,
+                                           unsigned row, double rns2, bool img, int& over,
+                                           int& most) {
+  const int lane = threadIdx.x & (MD_WAVE - 1);
+  const int col = lane & 3, seg = lane >> 2;
+  const int pad = (S & 4) ? 0 : 4;  // rows of 4 mod 8 records: the LDS reads meet no bank twice
+  const int S1 = S + pad;
+  const int ia = t + col;           // this lane's atom of the cell
+  const float rns2f = (float)rns2;
+  // the atom's own record, as a candidate
+  float u[4] = {0.0f, 0.0f, 0.0f, 0.0f}, cv = 1e30f, a2 = 0.0f;
+  const int v_own = own + min(ia, na - 1);
+  if (ia < na) {
+    const f32x4 q = *reinterpret_cast<const f32x4*>(recs[v_own + pad * segment_of(v_own, S)]);
 #pragma unroll
-  for (int o = 1; o < 32; o <<= 1) {
-    const int u = __shfl_up(incl, o, MD_WAVE);
-    if (lane >= o) incl += u;
+    for (int k = 0; k < 3; ++k) u[k] = -0.5f * q[k];
+    u[3] = 1.0f;
+    a2 = q[3];
+    cv = a2 - rns2f;
   }
-  const int C = __builtin_amdgcn_readlane(incl, 31);
-  if (lane < 32) {
-    s_beg[w][lane] = lane < 27 ? incl - cnt : C;
-    s_start[w][lane] = start;
-    s_code[w][lane] = code;
-  }
-  if (lane == 0) s_beg[w][32] = C;
-  __builtin_amdgcn_wave_barrier();
-  // the block wraps (image flag for the force passes), and the test mode
-  bool img = false, small = false;
+  a2 = fmaxf(a2, __int_as_float(quad_perm<0xB1>(__float_as_int(a2))));
+  a2 = fmaxf(a2, __int_as_float(quad_perm<0x4E>(__float_as_int(a2))));
+  const float reach = 2.0f * __builtin_amdgcn_sqrtf(a2) + 1.05f * __builtin_amdgcn_sqrtf(rns2f);
+  const float tau = 9.6e-7f * (reach * reach + rns2f);  // (2^-20, rounded up)
+  // signs of the segment's two parts (first candidate in the highest bit), and the least
+  // magnitude, with cv as the part of the distance that the atom contributes
+  const int H[2] = {((S / 2) + 3) & ~3, S - (((S / 2) + 3) & ~3)};
+  unsigned m[2];
+  auto signs = [&](float c) {
+    float least = 1e30f;
+    m[0] = m[1] = 0u;
+    const float(*rec)[4] = recs + seg * S1 + col;
+    auto step = [&](int h, int q) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(rec[q + h * H[0]]);
+      f32x4 d = {c, c, c, c};
 #pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const int cq = q == 0 ? c0 : (q == 1 ? c1 : c2);
-    if (D.periodic[q]) {
-      img |= (D.nc[q] < 3) || cq == 0 || cq == D.nc[q] - 1;
-      small |= D.nc[q] < 5;
+      for (int k = 0; k < 4; ++k) d = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k], u[k], d, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        m[h] = __builtin_amdgcn_alignbit(m[h], __float_as_uint(d[e]), 31);
+        least = __builtin_amdgcn_fmed3f(fabsf(d[e]), least, 0.0f);  // the smaller
+      }
+    };
+    int q = 0;
+#pragma unroll 2
+    for (; q < H[1]; q += 4) {
+      step(0, q);
+      step(1, q);
     }
-  }
-  const bool fast = ((size_t)npad << lanes_log2) < ((size_t)1 << 24) &&
-                    (size_t)max_neigh * npad * sizeof(int) < ((size_t)1 << 32);
-  const int mode_ = small ? RINT : (img ? SHIFT : PLAIN);
-#define MD_CELL_LISTS(M, R24)                                                                   \
-  cell_lists<M, R24>(D, a0, na, C, s_beg[w], s_start[w], s_code[w], s_p[w], pos, neigh, nneigh, \
-                     max_neigh, lanes_log2, npad, rns2, img, ctl)
-  if (fast) {
-    if (mode_ == PLAIN) MD_CELL_LISTS(PLAIN, true);
-    else if (mode_ == SHIFT) MD_CELL_LISTS(SHIFT, true);
-    else MD_CELL_LISTS(RINT, true);
+    if (q < H[0]) step(0, q);
+    m[0] <<= 32 - H[0];
+    m[1] = H[1] ? m[1] << (32 - H[1]) : 0u;
+    return least;
+  };
+  const float least = signs(cv);
+  const int v0 = seg * S;
+  const int self = v_own - v0;  // the atom itself is no neighbour of its own
+  auto drop_self = [&]() {
+    if (self >= 0 && self < H[0]) m[0] &= ~(0x80000000u >> self);
+    if (self >= H[0] && self < S) m[1] &= ~(0x80000000u >> (self - H[0]));
+  };
+  if (__any(!(least >= tau))) {
+    signs(cv - tau);
+    drop_self();
+    const double4 pi = pos[a0 + min(ia, na - 1)];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      unsigned left = m[h];
+      while (left) {
+        const int z = __clz(left);
+        const unsigned bit = 0x80000000u >> z;
+        left ^= bit;
+        const int v = v0 + h * H[0] + z;
+        const f32x4 r = *reinterpret_cast<const f32x4*>(recs[v + pad * seg]);
+        const double4 q = pos[cand[v]];
+        const double x[3] = {q.x, q.y, q.z}, xi[3] = {pi.x, pi.y, pi.z};
+        double d[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          // x_j - L k = centre + u: the image is what the record was staged with
+          const double im = rint(((x[k] - s.ctr[k]) + 0.5 * (double)r[k]) * D.inv_len[k]);
+          d[k] = (x[k] - xi[k]) - im * D.len[k];
+        }
+        const double r2 = (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2];
+        if (!(r2 < rns2)) m[h] ^= bit;
+      }
+    }
   } else {
-    if (mode_ == PLAIN) MD_CELL_LISTS(PLAIN, false);
-    else if (mode_ == SHIFT) MD_CELL_LISTS(SHIFT, false);
-    else MD_CELL_LISTS(RINT, false);
+    drop_self();
   }
-#undef MD_CELL_LISTS
+  // slots: the segments' counts in turn
+  const int n0 = __popc(m[0]), mine = n0 + __popc(m[1]);
+  // (within the four rows of 16 lanes, then across them)
+  int incl = mine;
+  incl += row_shr<4>(incl);
+  incl += row_shr<8>(incl);
+  const int r0 = __shfl(incl, 12 + col, MD_WAVE), r1 = __shfl(incl, 28 + col, MD_WAVE);
+  const int r2 = __shfl(incl, 44 + col, MD_WAVE), r3 = __shfl(incl, 60 + col, MD_WAVE);
+  incl += (lane >= 16 ? r0 : 0) + (lane >= 32 ? r1 : 0) + (lane >= 48 ? r2 : 0);
+  const int tot = r0 + r1 + r2 + r3;
+  // the two parts side by side, an entry of each per trip
+  const int lim = min(LSLOT, max_neigh);
+  unsigned short* list = s.list[w];
+  int slot[2] = {incl - mine, incl - mine + n0};
+  wave_sync();
+  if (!__any(tot > lim)) {
+    unsigned short* to[2] = {list + col * LSLOT + slot[0], list + col * LSLOT + slot[1]};
+    while (m[0] | m[1]) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (m[h] != 0u) {
+          const int z = __builtin_clz(m[h]);
+          *to[h]++ = (unsigned short)(v0 + h * H[0] + z);
+          m[h] &= 0x7fffffffu >> z;
+        }
+      }
+    }
+  } else {  // entries past the LDS slots go straight to memory, those past max_neigh nowhere
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      for (; m[h] != 0u; ++slot[h]) {
+        const int z = __builtin_clz(m[h]), v = v0 + h * H[0] + z;
+        m[h] &= 0x7fffffffu >> z;
+        if (slot[h] < lim) list[col * LSLOT + slot[h]] = (unsigned short)v;
+        else if (slot[h] < max_neigh) *entry(neigh, a0 + ia, slot[h], lanes_log2, row) = cand[v];
+      }
+    }
+  }
+  wave_sync();
+  if (lane < 4 && ia < na) {
+    nneigh[a0 + ia] = (tot < max_neigh ? tot : max_neigh) | (img ? MD_NN_IMG : 0);
+    over |= tot > max_neigh;
+    most = max(most, tot);
+  }
+  // rows: the four atoms' entries of a row are contiguous; a lane keeps its place in the row
+  // (W = 4 lanes ints, a divisor of 64) and steps over rows
+  const int W = 4 << lanes_log2, c = lane & (W - 1), i = c >> lanes_log2;
+  const int last = __shfl(min(ia < na ? tot : 0, lim), i, MD_WAVE);
+  int q = lane / W, at = (q << lanes_log2) + (c & ((1 << lanes_log2) - 1));
+  const int step = MD_WAVE / W;
+  int* to = neigh + ((size_t)(a0 + t) << lanes_log2) + (size_t)q * row + c;
+  for (; at < last; at += step << lanes_log2, to += (size_t)step * row)
+    *to = cand[list[i * LSLOT + at]];
+  wave_sync();
+}
+
+// One block per cell.  The fixed image of a stencil cell is the minimum image of every pair
+// that can be closer than r_ns when each periodic axis has at least three cells of edge w >
+// r_ns and every candidate lies in its cell; the second is checked while staging (|u| <= 1.5 w
+// per axis; not so if positions changed since the binning, left a wall or are not finite).
+// Cells for which either fails, or with more candidates than LDS holds, take the FP64 form,
+// their atoms shared among the wavefronts.
+//
+// Bound by latency: of 69 us for 131k Cu atoms (78 of 515 candidates accepted per atom, 41
+// MB of lists, an 8 us write) the vector units are busy for 46; finding the runs takes about 20,
+// the staging 10, the tests 20 and the entries the rest, much of it overlapped by the eight
+// blocks of a CU.  Before: one wavefront per cell testing 64 candidates against one atom at a
+// time in FP64, 118 us (98 us without its same-address atomics, see publish_counts); 864,000
+// argon atoms 361 us, 541 before.  Entries stored one by one as they are found (scattered words,
+// 11 per instruction) took 44 us of such a build, and 16 atoms per matrix instruction (two
+// groups for the 19 atoms of a cell, the second nearly empty) left the lanes a fifth full while
+// listing: 114 us.  Three wavefronts per block 76 us, two 78, five 88.
+__global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
+                                                         const double4* __restrict__ pos,
+                                                         const int* __restrict__ cell_start,
+                                                         int* neigh, int* nneigh, int max_neigh,
+                                                         int lanes_log2, int npad, double rns2,
+                                                         int seg, md_ctl_dev* ctl) {
+  if (skip_rebuild(mode, ctl)) return;
+  extern __shared__ double s_dyn[];
+  __shared__ CellLds s;
+  float(*recs)[4] = reinterpret_cast<float(*)[4]>(s_dyn);
+  int* cand = reinterpret_cast<int*>(recs + 16 * (seg + 4));
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / MD_WAVE);
+  const int lane = threadIdx.x & (MD_WAVE - 1);
+  const int cell = md_remap_block(b.n_cells);
+  if (cell >= b.n_cells) return;
+  if (w == 0) {
+    const int a0 = __builtin_amdgcn_readfirstlane(cell_start[cell]);
+    const int na = __builtin_amdgcn_readfirstlane(cell_start[cell + 1]) - a0;
+    // the box of this cell: the last domain whose cells start at or before it
+    int lo = 0, hi = b.n_rep - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (b.domains[mid].cell_off <= cell) lo = mid; else hi = mid - 1;
+    }
+    const md_domain& D = b.domains[lo];
+    const int local = cell - D.cell_off;
+    const int cc[3] = {local / (D.nc[2] * D.nc[1]), (local / D.nc[2]) % D.nc[1], local % D.nc[2]};
+    // lane t < 27 takes stencil cell (t / 9, t / 3 % 3, t % 3): its atom range and image
+    int cnt = 0, start = 0, k[3] = {0, 0, 0};
+    if (lane < 27) {
+      const int qx = stencil_cell(cc[0], lane / 9, D.nc[0], D.periodic[0], k[0]);
+      const int qy = stencil_cell(cc[1], (lane / 3) % 3, D.nc[1], D.periodic[1], k[1]);
+      const int qz = stencil_cell(cc[2], lane % 3, D.nc[2], D.periodic[2], k[2]);
+      if (qx >= 0 && qy >= 0 && qz >= 0) {
+        const int q = D.cell_off + (qx * D.nc[1] + qy) * D.nc[2] + qz;
+        start = cell_start[q];
+        cnt = cell_start[q + 1] - start;
+      }
+    }
+    // exclusive prefix of the range sizes over the lanes
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+      const int u = __shfl_up(incl, o, MD_WAVE);
+      if (lane >= o) incl += u;
+    }
+    const int C = __builtin_amdgcn_readlane(incl, 31);
+    const int beg = incl - cnt;
+    // the block wraps (image flag for the force passes)
+    bool img = false, fixed = C <= 16 * seg;
+    double off[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const double width = __builtin_amdgcn_rcp(D.inv_w[q]);  // (to 1e-7: its uses have slack)
+      const double ctr = D.lo[q] + (cc[q] + 0.5) * width;
+      off[q] = (double)k[q] * D.len[q] + ctr;
+      if (lane == 0) {
+        s.ctr[q] = ctr;
+        s.edge[q] = 1.5 * width * (1.0 + 1e-6);
+      }
+      if (D.periodic[q]) {
+        img |= (D.nc[q] < 3) || cc[q] == 0 || cc[q] == D.nc[q] - 1;
+        // two cells hold both images of a pair; cells no wider than r_ns leave none to rounding
+        fixed &= D.nc[q] >= 3 && width * width > rns2 * (1.0 + 1e-4);
+      }
+    }
+    const int key = (k[0] * 3 + k[1]) * 3 + k[2];
+    const bool joins = lane > 0 && lane < 27 && __shfl_up(start + cnt, 1, MD_WAVE) == start &&
+                       __shfl_up(key, 1, MD_WAVE) == key;
+    const unsigned long long heads = __builtin_amdgcn_ballot_w64(lane < 27 && !joins);
+    if (lane < 27 && !joins) {
+      const int r = lanes_below(heads);
+      s.run_v[r] = beg;
+      s.run_j[r] = start;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s.run_off[r][q] = off[q];
+    }
+    if (lane < 32) {
+      s.beg[lane] = lane < 27 ? beg : C;
+      s.start[lane] = start;
+    }
+    if (lane == 13) s.own = beg;
+    if (lane == 0) {
+      s.beg[32] = C;
+      s.n_runs = (int)__popcll(heads);
+      s.run_v[(int)__popcll(heads)] = C;
+      s.C = C;
+      s.a0 = a0;
+      s.na = na;
+      s.img = img;
+      s.fixed = fixed;
+      s.rep = lo;
+    }
+  }
+  __syncthreads();
+  auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  const int na = uniform(s.na);
+  if (na == 0) return;
+  const int a0 = uniform(s.a0), C = uniform(s.C);
+  const md_domain& D = b.domains[uniform(s.rep)];
+  const bool img = uniform(s.img) != 0;
+  bool fixed = uniform(s.fixed) != 0;
+  int over = 0, most = 0;
+  const int S = (C + 63) / 64 * 4;  // candidates per segment
+  if (fixed) {
+    const int pad = (S & 4) ? 0 : 4, n_runs = uniform(s.n_runs);
+    const double ex = s.edge[0], ey = s.edge[1], ez = s.edge[2];
+    bool bad = false;
+    for (int r = w; r < n_runs; r += CW) {
+      const int v0 = uniform(s.run_v[r]), n = uniform(s.run_v[r + 1]) - v0;
+      const int j0 = uniform(s.run_j[r]);
+      const double ox = s.run_off[r][0], oy = s.run_off[r][1], oz = s.run_off[r][2];
+      for (int q = lane; q < n; q += MD_WAVE) {
+        const double4 p = pos[j0 + q];
+        const double ux = p.x - ox, uy = p.y - oy, uz = p.z - oz;
+        bad |= !(fabs(ux) <= ex && fabs(uy) <= ey && fabs(uz) <= ez);
+        const float x = (float)ux, y = (float)uy, z = (float)uz;
+        const int v = v0 + q;
+        *reinterpret_cast<f32x4*>(recs[v + pad * segment_of(v, S)]) =
+            f32x4{-2.0f * x, -2.0f * y, -2.0f * z, x * x + y * y + z * z};
+        cand[v] = j0 + q;
+      }
+    }
+    for (int v = C + threadIdx.x; v < 16 * S; v += CELL_BLOCK)  // past the last: far away
+      *reinterpret_cast<f32x4*>(recs[v + pad * segment_of(v, S)]) =
+          f32x4{0.0f, 0.0f, 0.0f, 1e30f};
+    fixed = !__syncthreads_or(bad);
+  }
+  if (fixed) {
+    const int own = uniform(s.own);
+    for (int t = 4 * w; t < na; t += 4 * CW)
+      atom_lists(D, a0, na, t, S, own, s, recs, cand, w, pos, neigh, nneigh, max_neigh, lanes_log2,
+                 (unsigned)npad << lanes_log2, rns2, img, over, most);
+  } else {
+    const int per = (na + CW - 1) / CW, first = min(na, w * per), n = min(na, first + per) - first;
+    if (n > 0)
+      cell_lists(D, a0 + first, n, C, s.beg, s.start, (double(*)[MD_WAVE])s_dyn + 3 * w, pos, neigh, nneigh, max_neigh,
+                 lanes_log2, npad, rns2, img, over, most);
+  }
+  publish_counts(over, most, ctl);
 }
 
 }  // namespace
@@ -580,10 +852,15 @@ extern "C" int md_build_neighbors(const md_batch* b, md_rebuild_mode mode, const
   if (lg < 0 || nl->max_neigh < nl->lanes || nl->max_neigh % nl->lanes) return MD_ERR_ARG;
   if (!(b->r_ns > 0.0)) return MD_ERR_ARG;
   if (b->n_atoms == 0) return MD_OK;
-  const dim3 grid(md_grid_blocks((b->n_cells + CW - 1) / CW)), block(CELL_BLOCK);
-  MD_LAUNCH_TIMED(MD_KERNEL_BUILD, k_build, grid, block, 0, (hipStream_t)stream, *b, (int)mode,
-                  (const double4*)pos, cell_start, nl->neigh, nl->nneigh, nl->max_neigh, lg,
-                  md_npad(b->n_atoms), b->r_ns * b->r_ns, (md_ctl_dev*)ctl);
+  const dim3 grid(md_grid_blocks(b->n_cells)), block(CELL_BLOCK);
+  // LDS for 1.2 times the average number of candidates, at least 640 (eight blocks then share a
+  // CU) and at most 1024; cells with more take the FP64 form
+  const double avg = 27.0 * b->n_atoms / b->n_cells;
+  const int seg = std::min(SEG_MAX, std::max(40, (int)(1.2 * avg / 16.0 + 4.0) / 4 * 4));
+  MD_LAUNCH_TIMED(MD_KERNEL_BUILD, k_build, grid, block, candidate_lds(seg), (hipStream_t)stream,
+                  *b, (int)mode, (const double4*)pos, cell_start, nl->neigh, nl->nneigh,
+                  nl->max_neigh, lg, md_npad(b->n_atoms), b->r_ns * b->r_ns, seg,
+                  (md_ctl_dev*)ctl);
   MD_LAUNCH_CHECK();
   return MD_OK;
 }

@@ -1,0 +1,148 @@
+"""md_build_neighbors entry by entry: the lists of every atom, in order, against the candidate
+order written out in numpy (stencil cell, then position in the cell; FP64 minimum image without
+fused multiply-adds), where the build changes its form or its path:
+
+  grids of 2 (both images of a pair in one cell), 3, 4 and more cells per axis, walled axes,
+  cells of one atom, of more than 64 and with more candidates than fit the staging
+  pairs at exactly r_ns (decided in FP64), lists longer than the LDS slots, max_neigh overflow
+  positions that left their cells since the binning
+"""
+import numpy as np
+import pytest
+
+import mdinputs as mi
+
+pytestmark = pytest.mark.gpu
+
+
+def _stencil(c, nc, periodic):
+    """Cells along one axis in stencil order (None: no cell)."""
+    if periodic and nc < 3:
+        return [t if t < nc else None for t in range(3)]
+    out = []
+    for q in (c - 1, c, c + 1):
+        out.append(q % nc if periodic else (q if 0 <= q < nc else None))
+    return out
+
+
+def _model(pos, cell_start, box, nc, r_ns):
+    lo, ln, per = box.as_arrays()
+    inv = np.where(per != 0, 1.0 / ln, 0.0)
+    rns2 = r_ns * r_ns
+    lists = [None] * len(pos)
+    for c in np.ndindex(*nc):
+        a = (c[0] * nc[1] + c[1]) * nc[2] + c[2]
+        atoms = np.arange(cell_start[a], cell_start[a + 1])
+        if not len(atoms):
+            continue
+        st = [_stencil(c[k], nc[k], per[k]) for k in range(3)]
+        cand = [np.arange(cell_start[q], cell_start[q + 1])
+                for x in st[0] for y in st[1] for z in st[2]
+                if x is not None and y is not None and z is not None
+                for q in [(x * nc[1] + y) * nc[2] + z]]
+        cand = np.concatenate(cand)
+        for i in atoms:
+            d = pos[cand] - pos[i]
+            for k in range(3):
+                if per[k]:
+                    d[:, k] = d[:, k] - ln[k] * np.rint(d[:, k] * inv[k])
+            r2 = (d[:, 0] * d[:, 0] + d[:, 1] * d[:, 1]) + d[:, 2] * d[:, 2]
+            lists[i] = cand[(r2 < rns2) & (cand != i)]
+    return lists
+
+
+def _check(pos, box, r_ns, lanes=4, max_neigh=128, move=None):
+    from paper_2511_22951_amd import _native as N
+    from paper_2511_22951_amd import md
+    import torch
+    plan = md.Plan([box], [len(pos)], r_ns)
+    st = md.State(plan, pos, None, N.MD_FP64)
+    nl = md.NeighborList(plan.n_atoms, max_neigh, lanes)
+    nl.neigh.fill_(-1)
+    md.md_bin_cells(st)
+    if move is not None:
+        st.pos[:, :3] += torch.as_tensor(move(st.n), device="cuda")
+    md.md_build_neighbors(st, nl)
+    p = st.pos[:, :3].cpu().numpy()
+    want = _model(p, st.cell_start.cpu().numpy(), box, plan.cells_per_axis[0], r_ns)
+    got = nl.host_lists()
+    longest = max(len(w) for w in want)
+    status, info = st.read_flags()
+    assert info["max_nneigh"] == longest
+    assert bool(info["flags"] & N.FLAG_NEIGH_OVERFLOW) == (longest > nl.max_neigh)
+    for i, (g, w) in enumerate(zip(got, want)):
+        assert np.array_equal(g, w[:nl.max_neigh]), i
+    return longest
+
+
+def _crystal(cells, a, sigma, seed=1, periodic=(1, 1, 1)):
+    pos, box = mi.fcc_lattice(*cells, a)
+    pos = pos + np.random.default_rng(seed).normal(0.0, sigma, pos.shape)
+    box = mi.Box(box.lo, box.len, periodic)
+    pos = mi.wrap_into_box(pos, box)
+    lo, ln, per = box.as_arrays()
+    return np.where(per, pos, np.clip(pos, lo, lo + ln)), box
+
+
+@pytest.mark.parametrize("lanes", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("cells", [(4, 4, 4), (5, 6, 8), (9, 7, 5)])
+def test_thermal_crystals(cells, lanes):
+    """2 x 2 x 2, 3 x 3 x 4 and 5 x 4 x 3 cells of 5.8 A and more."""
+    _check(*_crystal(cells, 3.615, 0.1), 5.8, lanes)
+
+
+@pytest.mark.parametrize("periodic", [(0, 0, 0), (1, 0, 1), (0, 1, 1), (1, 1, 0)])
+def test_walled_axes(periodic):
+    _check(*_crystal((6, 5, 8), 3.615, 0.1, periodic=periodic), 5.8)
+
+
+def test_pairs_at_the_radius():
+    """A perfect lattice whose third shell is the search radius to the last bit and beside it."""
+    a = 4.0
+    pos, box = mi.fcc_lattice(6, 6, 7, a)
+    for r in (a * np.sqrt(1.5), np.nextafter(a * np.sqrt(1.5), 0.0),
+              np.nextafter(a * np.sqrt(1.5), 9.0), a * np.sqrt(1.5) * (1 + 1e-7)):
+        _check(pos, box, float(r))
+
+
+def test_cells_as_wide_as_the_radius():
+    pos, box = _crystal((5, 5, 5), 3.6, 0.05)  # 18 A: three cells of exactly 6 A
+    _check(pos, box, 6.0)
+
+
+def test_sparse_gas():
+    """About one atom per cell, many cells empty."""
+    box = mi.Box((-3.0, 2.0, 0.0), (40.0, 31.0, 55.0), (1, 1, 1))
+    pos = np.random.default_rng(3).uniform(0.0, 1.0, (300, 3)) * box.len + box.lo
+    assert _check(pos, box, 5.0, lanes=2) < 20
+
+
+@pytest.mark.parametrize("lanes,max_neigh", [(1, 256), (4, 256), (2, 130), (8, 96)])
+def test_dense_lists(lanes, max_neigh):
+    """About 150 neighbours: past the LDS slots of an atom, and past max_neigh."""
+    longest = _check(*_crystal((8, 6, 6), 3.615, 0.1), 7.2, lanes, max_neigh)
+    assert 130 < longest < 256
+
+
+def test_more_candidates_than_the_staging_holds():
+    """About 300 neighbours, 2000 candidates and 75 atoms per cell (lists of up to 400)."""
+    box = mi.Box((0.0, 0.0, 0.0), (24.0, 25.0, 30.0), (1, 1, 1))
+    pos = np.random.default_rng(4).uniform(0.0, 1.0, (4000, 3)) * box.len
+    assert _check(pos, box, 5.0, lanes=2, max_neigh=512) > 130
+
+
+def test_uneven_density():
+    """A dense slab in a thin gas: cells on both sides of the staging limit in one launch."""
+    rng = np.random.default_rng(5)
+    box = mi.Box((0.0, 0.0, 0.0), (20.0, 20.0, 80.0), (1, 1, 0))
+    thin = rng.uniform(0.0, 1.0, (800, 3)) * box.len
+    dense = rng.uniform(0.0, 1.0, (2500, 3)) * (20.0, 20.0, 12.0) + (0.0, 0.0, 30.0)
+    _check(np.concatenate([thin, dense]), box, 5.0, lanes=4, max_neigh=512)
+
+
+@pytest.mark.parametrize("scale", [0.1, 1.0, 4.0])
+def test_positions_moved_since_the_binning(scale):
+    """The lists hold the pairs within r_ns among the binned stencils, whatever the positions."""
+    rng = np.random.default_rng(6)
+    _check(*_crystal((6, 7, 8), 3.615, 0.1), 5.8,
+           move=lambda n: rng.normal(0.0, scale, (n, 3)))
