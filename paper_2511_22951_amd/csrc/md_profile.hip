@@ -2,6 +2,8 @@
 // and slab profiles of the flow and thermodynamic fields.
 #include <math.h>
 
+#include <algorithm>
+
 #include "md_internal.h"
 
 namespace {
@@ -66,7 +68,9 @@ __device__ __forceinline__ size_t list_entry(int i, int m, int lanes, size_t npa
   return ((size_t)(m / lanes) * npad + (size_t)i) * lanes + (size_t)(m % lanes);
 }
 
-// EAM, first pass: rhobar_i, F(rhobar_i), F'(rhobar_i), e_i = F + 1/2 sum_j phi(r_ij).
+// EAM with phi and rho on grids of their own, or with more coefficients than k_obs_eam keeps in
+// LDS, or lists of another shape: an atom per lane, coefficients through the caches.
+// First pass: rhobar_i, F(rhobar_i), F'(rhobar_i), e_i = F + 1/2 sum_j phi(r_ij).
 __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_obs_eam_rho(md_batch b, md_eam p,
                                                                const double4* pos, md_nlist nl,
                                                                size_t npad, double* e_atom,
@@ -141,6 +145,179 @@ __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_obs_eam_w(md_batch b, md_eam 
   });
 }
 
+// The EAM passes on lists of LANES lanes per atom, with the phi and rho coefficients (one grid)
+// staged in LDS as pairs {rho, phi}: the four a pair of atoms needs are four 16-byte LDS reads.
+// A wavefront takes 64 / LANES atoms of a tile, lane l of an atom its entries l, l + LANES, ..
+// (a coalesced read of the list), four in flight; blocks stride over the batch, so that the
+// staging is paid a few times per CU.
+//
+// Bound by the neighbours' gathers (the texture-data path is 98 % busy; VALU 38 %).  640,000 Al
+// atoms, lists of four lanes: 264 us and 287 us for the two passes, against 379 and 413 with an
+// atom per lane and coefficients through the caches (eight more divergent loads per pair).
+// Holding the kernels to 80 registers (six wavefronts per SIMD) spills: 317 and 621 us.
+constexpr int OBS_BLOCK = 512;
+constexpr int OBS_MAX_COEF = 4096;  // 64 KiB of LDS
+constexpr int OBS_GRID = 1024;      // four blocks per CU
+
+struct ObsGrid {
+  double x_lo, inv_h, h;
+  int n;  // coefficients
+};
+
+// sqrt(x) for a normal x > 0: the hardware estimate of 1 / sqrt(x) refined twice, then the
+// product's remainder added (within an ulp).
+__device__ __forceinline__ double sqrt_nr(double x, double& inv) {
+  double y = __builtin_amdgcn_rsq(x);
+  const double hx = 0.5 * x;
+#pragma unroll
+  for (int it = 0; it < 2; ++it) y = fma(y, fma(-hx * y, y, 0.5), y);
+  const double g = x * y;
+  inv = y;
+  return fma(fma(-g, g, x), 0.5 * y, g);
+}
+
+// Interval and local coordinate of r (the end intervals extend past the grid), and the four
+// coefficient pairs of the interval.
+__device__ __forceinline__ double obs_interval(const ObsGrid& G, const double2* c, double r,
+                                               double2 (&q)[4], bool& oor) {
+  const double u = (r - G.x_lo) * G.inv_h;
+  oor |= !(u >= 0.0 && u <= (double)(G.n - 3));
+  const double f = fmin(fmax(floor(u), 0.0), (double)(G.n - 4));
+  const int k = (int)f;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) q[m] = c[k + m];
+  return u - f;
+}
+
+// body(pos_j, j) for this lane's entries of the list of atom i.
+template <int LANES, typename Load, typename Body>
+__device__ __forceinline__ void obs_visit(const int* nb, size_t stride, int cnt, int self,
+                                          Load load, Body body) {
+  constexpr int U = 4;
+  if (cnt <= 0) return;
+  int jn[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) jn[u] = nb[u < cnt ? u * stride : 0];
+  for (int m0 = 0; m0 < cnt; m0 += U) {
+    decltype(load(0)) q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) q[u] = load(m0 + u < cnt ? jn[u] : self);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int m = m0 + U + u;
+      jn[u] = nb[m < cnt ? m * stride : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (m0 + u < cnt) body(q[u]);
+  }
+}
+
+struct ObsRec {
+  double x, y, z, fp;
+};
+
+// PASS 0: rho_fp = {rhobar_i, F'(rhobar_i)}, e_i = F + 1/2 sum phi.  PASS 1: w_i (F' read from
+// rho_fp).  The same formulas as k_obs_eam_rho and k_obs_eam_w.
+template <int LANES, int PASS>
+__global__ __launch_bounds__(OBS_BLOCK) void k_obs_eam(md_batch b, md_eam p, ObsGrid G,
+                                                       const double4* __restrict__ pos,
+                                                       md_nlist nl, size_t npad, double* rho_fp,
+                                                       double* out, md_ctl_dev* ctl) {
+  extern __shared__ double2 s_c[];
+  for (int k = threadIdx.x; k < G.n; k += blockDim.x)
+    s_c[k] = make_double2(p.rho.coef[k], p.phi.coef[k]);
+  __syncthreads();
+  constexpr int WAVES = OBS_BLOCK / MD_WAVE;
+  const int lane = threadIdx.x & (MD_WAVE - 1), l = lane % LANES;
+  const int n = b.n_atoms, units = b.n_tiles * LANES, nlb = (units + WAVES - 1) / WAVES;
+  const double rc2 = p.r_cut * p.r_cut;
+  const double* fp = rho_fp + n;
+  bool oor = false;
+  for (int k = 0;; ++k) {
+    const int lb = md_remap_stride(nlb, k);
+    if (lb >= nlb) break;
+    const int unit = lb * WAVES + (int)(threadIdx.x / MD_WAVE);
+    if (unit >= units) continue;
+    const md_tile T = b.tiles[unit / LANES];
+    const int a = (unit % LANES) * (MD_WAVE / LANES) + lane / LANES;
+    if (a >= T.count) continue;  // (whole groups of LANES lanes)
+    const int i = T.first + a;
+    const md_domain& D = b.domains[T.rep];
+    const double4 pi = pos[i];
+    const double fpi = PASS ? fp[i] : 0.0;
+    const int nn = nl.nneigh[i] & MD_NN_MASK;
+    const int cnt = nn > l ? (nn - l + LANES - 1) / LANES : 0;
+    double rho = 0.0, phi = 0.0, w[6] = {0, 0, 0, 0, 0, 0};
+    obs_visit<LANES>(
+        nl.neigh + (size_t)i * LANES + l, npad * LANES, cnt, i,
+        [&](int j) {
+          const double4 q = pos[j];
+          return ObsRec{q.x, q.y, q.z, PASS ? fp[j] : 0.0};
+        },
+        [&](const ObsRec& q) {
+          double d[3];
+          min_image(D, pi, make_double4(q.x, q.y, q.z, 0.0), d);
+          const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+          if (!(r2 < rc2)) return;
+          double ir;
+          const double r = sqrt_nr(r2, ir);
+          double2 c[4];
+          const double t = obs_interval(G, s_c, r, c, oor);
+          const double v = 1.0 - t, t2 = t * t;
+          if (PASS == 0) {  // 6 b_m(t)
+            const double t3 = t2 * t;
+            const double bb[4] = {v * v * v, fma(t2, fma(3.0, t, -6.0), 4.0),
+                                  fma(3.0, t2 - t3, fma(3.0, t, 1.0)), t3};
+            double sr = 0.0, sp = 0.0;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+              sr = fma(c[m].x, bb[m], sr);
+              sp = fma(c[m].y, bb[m], sp);
+            }
+            rho += sr;
+            phi += sp;
+          } else {  // 2 h b'_m(t)
+            const double bb[4] = {-(v * v), t * fma(3.0, t, -4.0), fma(-3.0, t2, fma(2.0, t, 1.0)),
+                                  t2};
+            double dr = 0.0, dp = 0.0;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+              dr = fma(c[m].x, bb[m], dr);
+              dp = fma(c[m].y, bb[m], dp);
+            }
+            const double s = fma(fpi + q.fp, dr, dp) * ir;  // -2 h f_ij = s r_ij
+            const double sx = s * d[0], sy = s * d[1], sz = s * d[2];
+            w[0] = fma(sx, d[0], w[0]);
+            w[1] = fma(sy, d[1], w[1]);
+            w[2] = fma(sz, d[2], w[2]);
+            w[3] = fma(sx, d[1], w[3]);
+            w[4] = fma(sx, d[2], w[4]);
+            w[5] = fma(sy, d[2], w[5]);
+          }
+        });
+    if (PASS == 0) {
+      rho = md_group_sum<LANES>(rho) / 6.0;
+      phi = md_group_sum<LANES>(phi) / 6.0;
+      if (l == 0) {
+        double f1;
+        const double F = spl_eval(spl(p.emb), rho, f1, oor);
+        out[i] = F + 0.5 * phi;
+        rho_fp[i] = rho;
+        rho_fp[n + i] = f1;
+      }
+    } else {
+      const double scale = -0.25 * G.inv_h;  // 1/2 of the virial, 1 / (2 h), f_ij's sign
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        const double s = md_group_sum<LANES>(w[q]);
+        if (l == 0) out[(size_t)q * n + i] = s * scale;
+      }
+    }
+  }
+  if (PASS == 0 && __any(oor) && lane == 0) md_flag(ctl, MD_FLAG_TABLE_RANGE);
+}
+
 // Lennard-Jones: e_i = 1/2 sum_j U(r_ij) (shifted), w_i = 1/2 sum_j r_ij (x) f_ij with
 // f_ij = 24 eps [2 (s/r)^12 - (s/r)^6] r_ij / r^2.
 __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_obs_lj(md_batch b, md_lj p, double ucut,
@@ -199,24 +376,51 @@ __device__ __forceinline__ int bin_of(const md_domain& D, const ProfGeom& G, con
   return (q >= 0.0 && q < (double)G.n_bins) ? (int)q : -1;
 }
 
+// Wave-wide sums of v[0..N) spread over the lanes: each stage halves the values a lane still
+// carries by exchanging the other half with its partner (a single value is added up).  On
+// return v[0] is the sum of element `at`, the same in all lanes that carry it.
+template <int N, int O, int W>
+__device__ __forceinline__ void wave_sum_scatter(double (&v)[W], int& at) {
+  if constexpr (O > 0) {
+    if constexpr (N > 1) {
+      const bool up = (threadIdx.x & O) != 0;
+#pragma unroll
+      for (int q = 0; q < N / 2; ++q) {
+        const double keep = up ? v[q + N / 2] : v[q], give = up ? v[q] : v[q + N / 2];
+        v[q] = keep + __shfl_xor(give, O, MD_WAVE);
+      }
+      at += up ? N / 2 : 0;
+      wave_sum_scatter<N / 2, O / 2, W>(v, at);
+    } else {
+      v[0] += __shfl_xor(v[0], O, MD_WAVE);
+      wave_sum_scatter<1, O / 2, W>(v, at);
+    }
+  }
+}
+
 // Add v[0..NQ) of every lane into acc[bin * NACC + base + q]: one wave-wide sum and
-// one integer atomic per distinct bin of the wave (atoms in cell order share few bins).
+// one integer atomic per distinct bin of the wave (atoms in cell order share few bins: the
+// cells of a wavefront follow one another along z, about five slabs of it).  The sums of a bin
+// are made together, 20 exchanges for the 11 of the first pass where one at a time took 66:
+// 640,000 atoms 24 and 25 us for the two passes, 74 and 48 before (HBM floor 14 and 7).
 template <int NQ>
 __device__ __forceinline__ void wave_bin_add(int bin, const double (&v)[NQ], long long* acc,
                                              int base) {
+  constexpr int W = NQ <= 8 ? 8 : 16;
   unsigned long long left = __ballot(bin >= 0);
   const int lane = threadIdx.x & (MD_WAVE - 1);
   while (left) {
     const int leader = __ffsll((long long)left) - 1;
     const int lb = __shfl(bin, leader, MD_WAVE);
     const bool mine = bin == lb;
+    double s[W];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const double s = md_wave_sum(mine ? v[q] : 0.0);
-      if (lane == 0)
-        atomicAdd((unsigned long long*)&acc[(size_t)lb * NACC + base + q],
-                  (unsigned long long)(long long)rint(s * PROF_SCALE));
-    }
+    for (int q = 0; q < W; ++q) s[q] = q < NQ && mine ? v[q < NQ ? q : 0] : 0.0;
+    int at = 0;
+    wave_sum_scatter<W, MD_WAVE / 2>(s, at);
+    if (lane % (MD_WAVE / W) == 0 && at < NQ)
+      atomicAdd((unsigned long long*)&acc[(size_t)lb * NACC + base + at],
+                (unsigned long long)(long long)rint(s[0] * PROF_SCALE));
     left &= ~__ballot(mine);
   }
 }
@@ -360,6 +564,33 @@ extern "C" int md_atom_observables(const md_batch* b, const md_eam* eam, const m
   if (!spline_ok(eam->phi) || !spline_ok(eam->rho) || !spline_ok(eam->emb) || !rho_fp ||
       !(eam->r_cut > 0.0))
     return MD_ERR_ARG;
+  // LDS-staged coefficients where phi and rho share a grid of at most OBS_MAX_COEF (every
+  // tabulated potential of up to 4094 samples)
+  const int L = nl->lanes;
+  const bool pow2 = L == 1 || L == 2 || L == 4 || L == 8 || L == 16;
+  if (pow2 && eam->phi.ncoef == eam->rho.ncoef && eam->phi.x_lo == eam->rho.x_lo &&
+      eam->phi.h == eam->rho.h && eam->rho.ncoef <= OBS_MAX_COEF) {
+    const ObsGrid G{eam->rho.x_lo, 1.0 / eam->rho.h, eam->rho.h, eam->rho.ncoef};
+    const size_t lds = (size_t)G.n * sizeof(double2);
+    const int nlb = (b->n_tiles * L + OBS_BLOCK / MD_WAVE - 1) / (OBS_BLOCK / MD_WAVE);
+    const dim3 og(std::min(md_grid_blocks(nlb), OBS_GRID)), ob(OBS_BLOCK);
+#define MD_OBS_LAUNCH(LN)                                                                        \
+  hipLaunchKernelGGL((k_obs_eam<LN, 0>), og, ob, lds, st, *b, *eam, G, (const double4*)pos, *nl, \
+                     npad, rho_fp, e_atom, c);                                                   \
+  MD_LAUNCH_CHECK();                                                                             \
+  hipLaunchKernelGGL((k_obs_eam<LN, 1>), og, ob, lds, st, *b, *eam, G, (const double4*)pos, *nl, \
+                     npad, rho_fp, w_atom, c);                                                   \
+  MD_LAUNCH_CHECK()
+    switch (L) {
+      case 1: MD_OBS_LAUNCH(1); break;
+      case 2: MD_OBS_LAUNCH(2); break;
+      case 4: MD_OBS_LAUNCH(4); break;
+      case 8: MD_OBS_LAUNCH(8); break;
+      default: MD_OBS_LAUNCH(16); break;
+    }
+#undef MD_OBS_LAUNCH
+    return MD_OK;
+  }
   hipLaunchKernelGGL(k_obs_eam_rho, grid, block, 0, st, *b, *eam, (const double4*)pos, *nl, npad,
                      e_atom, rho_fp, c);
   MD_LAUNCH_CHECK();
