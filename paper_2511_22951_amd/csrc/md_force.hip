@@ -117,14 +117,26 @@ __device__ __forceinline__ float cubic(const float* a, float t) {
   return ((a[3] * t + a[2]) * t + a[1]) * t + a[0];
 }
 
-// Blocks of the force passes: up to 1024 threads (md_nlist.block: 256, 512 or 1024, default
-// 1024), each block TPB work tiles of 64 atoms x LANES lanes.
+// Blocks of the force passes: up to 1024 threads (md_nlist.block: 256, 512 or 1024, or 0 for
+// block_threads' choice), each block TPB work tiles of 64 atoms x LANES lanes.
 constexpr int FBLOCK = 1024;
 template <int LANES>
 __device__ __forceinline__ int tiles_per_block() {
   return __builtin_amdgcn_readfirstlane((int)blockDim.x / (64 * LANES));
 }
-static inline int block_threads(const md_nlist& nl) { return nl.block ? nl.block : FBLOCK; }
+// md_nlist.block = 0: the smallest block whose grid leaves every block a CU of its own (256 of
+// them), else 1024.  Below that line 1024-thread blocks leave CUs idle and a few share the whole
+// gather traffic; above it smaller blocks only stage the LDS tables more often.  Both EAM passes,
+// us for 1024 / 512 / 256 threads: 8,788 atoms FP32 at 4 lanes 25.9 / 20.9 / 19.7, FP64 at 2
+// lanes 60.4 / 38.6 / 29.7 (at most 138 blocks); 32,000 atoms FP64 at 4 lanes 38.4 / 28.4 / 40.8
+// (125 / 250 / 500 blocks); 131,072 atoms FP32 at 2 lanes 47.5 / 47.7 / 62.1 (256 / 512 / 1024).
+// LJ, 256 atoms FP64 at 4 lanes 18.5 / 13.5 / 11.1; 32,000 at 2 lanes 28.7 / 19.5 / 17.9.
+static inline int block_threads(const md_nlist& nl, int n_tiles) {
+  if (nl.block) return nl.block;
+  for (int t = 256; t < FBLOCK; t *= 2)
+    if (t >= 64 * nl.lanes && (size_t)n_tiles * 64 * nl.lanes <= (size_t)256 * t) return t;
+  return FBLOCK;
+}
 
 // Where a thread sits: its tile (-1 if none), its atom slot and lane.
 struct Slot {
@@ -145,13 +157,31 @@ __device__ __forceinline__ Slot force_slot(int n_tiles) {
   return s;
 }
 
-// Stage a table of nrows rows of W values of type R into LDS (16-byte moves).
+// Stage a table of nrows rows of W values of type R into LDS (16-byte moves).  With sixteen and
+// more moves per thread (FP64 tables of 125 KB, small blocks) eight are in flight: one at a time
+// the round trips of a block added up, FP64 passes of 8,788 atoms with 256 threads 33.9 -> 29.7
+// us, of 131,072 with 1024 72.5 -> 70.5 us.  The four moves per thread of FP32 tables and full
+// blocks lose by it (131,072 atoms, 18 steps 979 -> 1003 us).
 template <typename R, int W>
 __device__ __forceinline__ const R* stage_table(const R* g, int nrows, R* lds) {
   const int n16 = nrows * W * (int)sizeof(R) / 16;
   const float4* src = reinterpret_cast<const float4*>(g);
   float4* dst = reinterpret_cast<float4*>(lds);
-  for (int q = threadIdx.x; q < n16; q += blockDim.x) dst[q] = src[q];
+  int q = threadIdx.x;
+  const int step = blockDim.x;
+  if (sizeof(R) == 8 || step < 1024) {
+    for (; q + 7 * step < n16; q += 8 * step) {
+      float4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = src[q + u * step];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) dst[q + u * step] = v[u];
+    }
+#pragma unroll 4
+    for (; q < n16; q += step) dst[q] = src[q];
+  } else {
+    for (; q < n16; q += step) dst[q] = src[q];
+  }
   __syncthreads();
   return lds;
 }
@@ -1000,7 +1030,7 @@ bool nlist_ok(const md_nlist* nl) {
   if (!nl || !nl->neigh || !nl->nneigh) return false;
   const int L = nl->lanes;
   if (L != 1 && L != 2 && L != 4 && L != 8 && L != 16) return false;
-  const int B = block_threads(*nl);
+  const int B = nl->block ? nl->block : FBLOCK;
   if ((B != 256 && B != 512 && B != 1024) || B < 64 * L) return false;
   return nl->max_neigh >= L && nl->max_neigh % L == 0;
 }
@@ -1055,7 +1085,7 @@ int launch_eam(const md_batch& b, const md_eam& p, const char* tab, const md_tab
   g.q_lo = qg.q_lo;
   g.q_inv_h = 1.0 / qg.h;
   const R rc2 = (R)(p.r_cut * p.r_cut);
-  const int bt = block_threads(nl), TPB = bt / (64 * LANES);
+  const int bt = block_threads(nl, b.n_tiles), TPB = bt / (64 * LANES);
   const dim3 grid(md_grid_blocks((b.n_tiles + TPB - 1) / TPB)), block(bt);
   const int npad = md_npad(b.n_atoms);
   const R* rtab = (const R*)(tab + TL.rtab);
@@ -1148,7 +1178,7 @@ void launch_lj(const md_batch& b, const md_lj& p, const double* pos, const md_nl
   const double src6 = pow(p.sigma / p.r_cut, 6.0);
   c.ucut = 4.0 * p.eps * (src6 * src6 - src6);
   const R rc2 = (R)(p.r_cut * p.r_cut);
-  const int bt = block_threads(nl), TPB = bt / (64 * LANES);
+  const int bt = block_threads(nl, b.n_tiles), TPB = bt / (64 * LANES);
   const dim3 grid(md_grid_blocks((b.n_tiles + TPB - 1) / TPB)), block(bt);
   const int npad = md_npad(b.n_atoms);
   const bool big = md_big_list(nl, npad);
@@ -1208,7 +1238,7 @@ static int drift_load(const md_batch* b, const md_nlist* nl, const double* pos, 
   dr->rec_in = (uint4*)drift->rec_in;
   dr->rec_out = (uint4*)drift->rec_out;
   dr->rec_current = drift->rec_in && drift->rec_current ? 1 : 0;
-  const int tpb = block_threads(*nl) / (64 * nl->lanes);
+  const int tpb = block_threads(*nl, b->n_tiles) / (64 * nl->lanes);
   if (md_grid_blocks((b->n_tiles + tpb - 1) / tpb) > MD_DMAX_SLOTS) return MD_ERR_ARG;
   return MD_OK;
 }

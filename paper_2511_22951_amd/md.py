@@ -100,7 +100,7 @@ class NeighborList:
     """Padded strided ELL list (md_nlist) for `lanes` lanes per atom."""
 
     def __init__(self, n_atoms, max_neigh=128, lanes=4, device="cuda", block=0):
-        """block: threads per workgroup of the force passes (0: the library default, 1024)."""
+        """block: threads per workgroup of the force passes (0: chosen by the library)."""
         if max_neigh % lanes:
             max_neigh += lanes - max_neigh % lanes
         self.n, self.max_neigh, self.lanes, self.block = n_atoms, max_neigh, lanes, int(block)
