@@ -146,3 +146,27 @@ def test_positions_moved_since_the_binning(scale):
     rng = np.random.default_rng(6)
     _check(*_crystal((6, 7, 8), 3.615, 0.1), 5.8,
            move=lambda n: rng.normal(0.0, scale, (n, 3)))
+
+
+@pytest.mark.parametrize("lanes", [1, 4])
+def test_batch_of_uneven_boxes(lanes):
+    """About 370, 870 and 1700 candidates per cell in one launch: the lists of each box alone."""
+    from paper_2511_22951_amd import md
+    boxes = [_crystal(c, a, 0.1, seed) for c, a, seed in
+             [((6, 6, 6), 3.95, 6), ((6, 6, 6), 3.45, 7), ((5, 5, 5), 3.45, 8), ((9, 7, 6), 3.7, 9)]]
+
+    def lists(sel):
+        plan = md.Plan([b for _, b in sel], [len(p) for p, _ in sel], 5.8)
+        st = md.State(plan, np.concatenate([p for p, _ in sel]), None, 0)
+        nl = md.NeighborList(plan.n_atoms, 128, lanes)
+        md.md_bin_cells(st)
+        md.md_build_neighbors(st, nl)
+        st.check_flags()
+        return nl.host_lists()
+
+    got = lists(boxes)
+    first = 0
+    for p, b in boxes:
+        for i, w in enumerate(lists([(p, b)])):
+            assert np.array_equal(got[first + i] - first, w), (first, i)
+        first += len(p)
