@@ -50,36 +50,59 @@ __device__ __forceinline__ int lanes_below(unsigned long long m) {
                                         __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
-__global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bin_count(md_batch b, int mode, double4* pos,
-                                                             int* cell_of, int* rank_of,
-                                                             int* counts, md_ctl_dev* ctl) {
+// x wrapped into the box (x <- x - L floor((x - lo) / L); a result of lo + L goes to lo) and its
+// cell; problems are added to bad.
+__device__ __forceinline__ int wrap_and_cell(const md_domain& D, double4& p, int& bad) {
+  double x[3] = {p.x, p.y, p.z};
+  int c[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (!isfinite(x[a])) bad |= MD_FLAG_NONFINITE;
+    if (D.periodic[a]) {
+      double y = x[a] - D.len[a] * floor((x[a] - D.lo[a]) / D.len[a]);
+      if (y >= D.lo[a] + D.len[a]) y = D.lo[a];
+      x[a] = y;
+    } else if (x[a] < D.lo[a] || x[a] > D.lo[a] + D.len[a]) {
+      bad |= MD_FLAG_WALL;
+    }
+    c[a] = cell_coord(x[a], D.lo[a], D.inv_w[a], D.nc[a]);
+  }
+  p.x = x[0];
+  p.y = x[1];
+  p.z = x[2];
+  return D.cell_off + (c[0] * D.nc[1] + c[1]) * D.nc[2] + c[2];
+}
+
+// The wrapped positions, velocities and ids also go to their copies, from which the gather writes
+// the sorted arrays: each atom's record is read and written twice.  With the gather writing the
+// copies and a fifth launch copying them back (three times each) the three kernels that touch the
+// records took 25 + 34 + 21 us for 640,000 atoms and 47 + 86 + 58 us for 2,048,000, now 34 + 26
+// and 58 + 84 us.
+__global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bin_count(md_batch b, int mode,
+                                                             const double4* pos, const double* vel,
+                                                             const int* id, int* cell_of,
+                                                             int* rank_of, int* counts,
+                                                             double4* pos_s, double* vel_s,
+                                                             int* id_s, md_ctl_dev* ctl) {
   // The rebuild decision: every block reduces the displacement maxima of the last
   // drift itself (no cross-block communication); block 0 publishes it for the
   // other rebuild kernels of this call.
   const bool go = mode == MD_ALWAYS || md_displacement_exceeded(ctl);
   if (blockIdx.x == 0 && threadIdx.x == 0) ctl->rebuild = go ? 1 : 0;
   if (!go) return;
+  const int n = b.n_atoms;
   int bad = 0;
   FOR_ATOMS(b, i, T, {
     const md_domain& D = b.domains[T.rep];
     double4 p = pos[i];
-    double x[3] = {p.x, p.y, p.z};
-    int c[3];
-_Pragma("unroll")
-    for (int a = 0; a < 3; ++a) {
-      if (!isfinite(x[a])) bad |= MD_FLAG_NONFINITE;
-      if (D.periodic[a]) {
-        // x <- x - L floor((x - lo) / L); a result of lo + L goes to lo.
-        double y = x[a] - D.len[a] * floor((x[a] - D.lo[a]) / D.len[a]);
-        if (y >= D.lo[a] + D.len[a]) y = D.lo[a];
-        x[a] = y;
-      } else if (x[a] < D.lo[a] || x[a] > D.lo[a] + D.len[a]) {
-        bad |= MD_FLAG_WALL;
-      }
-      c[a] = cell_coord(x[a], D.lo[a], D.inv_w[a], D.nc[a]);
-    }
-    const int cell = D.cell_off + (c[0] * D.nc[1] + c[1]) * D.nc[2] + c[2];
-    pos[i] = make_double4(x[0], x[1], x[2], p.w);
+    const double v0 = vel[i], v1 = vel[n + i], v2 = vel[2 * n + i];
+    const int my = id[i];
+    const int cell = wrap_and_cell(D, p, bad);
+    pos_s[i] = p;
+    vel_s[i] = v0;
+    vel_s[n + i] = v1;
+    vel_s[2 * n + i] = v2;
+    id_s[i] = my;
     cell_of[i] = cell;
     // Histogram with one atomic per run of equal cells among the wavefront's atoms
     // (they are still nearly in cell order from the last rebuild), all runs' atomics
@@ -102,9 +125,8 @@ _Pragma("unroll")
   if (bad) md_flag(ctl, bad);
 }
 
-// 2. exclusive scan of the histogram into cell_start (counts reset), over
-// contiguous segments of cells, one 1024-thread block each: segment sums, one
-// block scanning the sums, then each block scanning its segment from its offset.
+// 2. exclusive scan of the histogram into cell_start.  The counts are reset by the scatter, when
+// no block reads them any more.
 __device__ __forceinline__ int block_incl_scan(int v, int* s_w, int& total) {
   const int lane = threadIdx.x & (MD_WAVE - 1), w = threadIdx.x / MD_WAVE;
   const int nw = blockDim.x / MD_WAVE;
@@ -131,33 +153,35 @@ __device__ __forceinline__ int block_incl_scan(int v, int* s_w, int& total) {
   return v;
 }
 
-// The whole histogram scan in one block, for grids of at most MD_SCAN_ONE_MAX cells: each
-// thread scans a contiguous run of cells (one launch instead of three).
-#define MD_SCAN_ONE_MAX 65536
-__global__ __launch_bounds__(1024) void k_scan_one(int n_cells, int mode, int* counts,
-                                                    int* cell_start, md_ctl_dev* ctl) {
+// A block per 1024 cells, each summing the counts before its own itself: one launch, no block
+// waits for another.  For grids of at most MD_SCAN_DIRECT_MAX cells (the last block then reads
+// 0.5 MB): 5 us for 37,000 cells, 7 us for 104,000.  One block scanning all cells, a run per
+// thread, took 66 us for the first, three launches 15 us for the second.
+#define MD_SCAN_DIRECT_MAX 131072
+__global__ __launch_bounds__(1024) void k_scan_direct(int n_cells, int mode, const int* counts,
+                                                       int* cell_start, md_ctl_dev* ctl) {
   if (skip_rebuild(mode, ctl)) return;
   __shared__ int s_w[17];
-  const int per = (n_cells + 1023) / 1024;
-  const int beg = min(n_cells, (int)threadIdx.x * per), end = min(n_cells, beg + per);
-  int v = 0;
-#pragma unroll 8
-  for (int k = beg; k < end; ++k) v += counts[k];
-  int total;
-  int run = block_incl_scan(v, s_w, total) - v;
-#pragma unroll 8
-  for (int k = beg; k < end; ++k) {
-    const int c = counts[k];
-    cell_start[k] = run;
-    run += c;
-    counts[k] = 0;
+  const int beg = blockIdx.x * 1024, k = beg + threadIdx.x;
+  const int v = k < n_cells ? counts[k] : 0;
+  int before = 0, carry, total;
+  const int4* c4 = reinterpret_cast<const int4*>(counts);
+#pragma unroll 4
+  for (int q = threadIdx.x; q < beg / 4; q += 1024) {
+    const int4 c = c4[q];
+    before += c.x + c.y + c.z + c.w;
   }
-  if (threadIdx.x == 0) {
-    cell_start[n_cells] = total;
+  block_incl_scan(before, s_w, carry);
+  const int incl = block_incl_scan(v, s_w, total);
+  if (k < n_cells) cell_start[k] = carry + incl - v;
+  if (k == n_cells - 1) {
+    cell_start[n_cells] = carry + total;
     ctl->n_rebuilds += 1;
   }
 }
 
+// Larger grids: contiguous segments of cells, one 1024-thread block each: segment sums, one
+// block scanning the sums, then each block scanning its segment from its offset.
 __global__ __launch_bounds__(1024) void k_scan_sums(int n_cells, int seg, int mode,
                                                      const int* counts, int* bsum,
                                                      md_ctl_dev* ctl) {
@@ -186,7 +210,7 @@ __global__ __launch_bounds__(1024) void k_scan_top(int nb, int n_cells, int mode
   }
 }
 
-__global__ __launch_bounds__(1024) void k_scan_apply(int n_cells, int seg, int mode, int* counts,
+__global__ __launch_bounds__(1024) void k_scan_apply(int n_cells, int seg, int mode, const int* counts,
                                                       const int* bsum, int* cell_start,
                                                       md_ctl_dev* ctl) {
   if (skip_rebuild(mode, ctl)) return;
@@ -198,21 +222,19 @@ __global__ __launch_bounds__(1024) void k_scan_apply(int n_cells, int seg, int m
     const int v = k < end ? counts[k] : 0;
     int total;
     const int incl = block_incl_scan(v, s_w, total);
-    if (k < end) {
-      cell_start[k] = carry + incl - v;
-      counts[k] = 0;
-    }
+    if (k < end) cell_start[k] = carry + incl - v;
     carry += total;
   }
 }
 
 // 3. scatter atom indices (and their ids) into their cell segments, at the slots
-//    the histogram handed out.
+//    the histogram handed out, and reset the histogram.
 __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bin_scatter(md_batch b, int mode,
                                                                const int* cell_of,
                                                                const int* rank_of,
                                                                const int* cell_start,
                                                                const int* id, int* src, int* sid,
+                                                               int* counts,
                                                                const md_ctl_dev* ctl) {
   if (skip_rebuild(mode, ctl)) return;
   FOR_ATOMS(b, i, T, {
@@ -220,53 +242,121 @@ __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bin_scatter(md_batch b, int m
     src[dst] = i;
     sid[dst] = id[i];
   });
+  for (int k = blockIdx.x * MD_ATOM_BLOCK + threadIdx.x; k < b.n_cells;
+       k += gridDim.x * MD_ATOM_BLOCK)
+    counts[k] = 0;
 }
 
-// 4. order each cell by atom id (rank sort inside the cell segment) and gather
-//    the atom records into the sorted copies.
+// 4. order each cell by atom id (rank sort inside the cell segment) and gather the atom records
+//    from their copies; the positions become the displacement reference.
 __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bin_gather(
     md_batch b, int mode, const int* cell_of, const int* cell_start, const int* src,
-    const int* sid, const double4* pos, const double* vel, double4* pos_s, double* vel_s,
-    int* id_s, const md_ctl_dev* ctl) {
-  if (skip_rebuild(mode, ctl)) return;
-  const int n = b.n_atoms;
-  FOR_ATOMS(b, slot, T, {
-    const int a = src[slot];
-    const int c = cell_of[a];
-    const int beg = cell_start[c], end = cell_start[c + 1];
-    const int my = sid[slot];
-    int rank = 0;  // ids are unique: the rank by id is a permutation of the segment
-    for (int k = beg; k < end; ++k) rank += sid[k] < my;
-    const int dst = beg + rank;
-    pos_s[dst] = pos[a];
-    vel_s[dst] = vel[a];
-    vel_s[n + dst] = vel[n + a];
-    vel_s[2 * n + dst] = vel[2 * n + a];
-    id_s[dst] = my;
-  });
-}
-
-// 5. copy the sorted records back and take them as the displacement reference.
-__global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bin_copyback(
-    md_batch b, int mode, const double4* pos_s, const double* vel_s, const int* id_s,
-    double4* pos, double* vel, int* id, double* pos_ref, md_ctl_dev* ctl) {
+    const int* sid, const double4* pos_s, const double* vel_s, double4* pos, double* vel,
+    int* id, double* pos_ref, md_ctl_dev* ctl) {
   if (skip_rebuild(mode, ctl)) return;
   const int n = b.n_atoms;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctl->n_dmax = 0;      // displacements now measured afresh
     ctl->rec_stale = 1;   // atoms reordered: carried-over neighbour records are void
   }
-  FOR_ATOMS(b, i, T, {
-    const double4 p = pos_s[i];
-    pos[i] = p;
-    vel[i] = vel_s[i];
-    vel[n + i] = vel_s[n + i];
-    vel[2 * n + i] = vel_s[2 * n + i];
-    id[i] = id_s[i];
-    pos_ref[i] = p.x;
-    pos_ref[n + i] = p.y;
-    pos_ref[2 * n + i] = p.z;
+  FOR_ATOMS(b, slot, T, {
+    const int a = src[slot];
+    const double4 p = pos_s[a];
+    const double v0 = vel_s[a], v1 = vel_s[n + a], v2 = vel_s[2 * n + a];
+    const int c = cell_of[a];
+    const int beg = cell_start[c], end = cell_start[c + 1];
+    const int my = sid[slot];
+    int rank = 0;  // ids are unique: the rank by id is a permutation of the segment
+    for (int k = beg; k < end; ++k) rank += sid[k] < my;
+    const int dst = beg + rank;
+    pos[dst] = p;
+    vel[dst] = v0;
+    vel[n + dst] = v1;
+    vel[2 * n + dst] = v2;
+    id[dst] = my;
+    pos_ref[dst] = p.x;
+    pos_ref[n + dst] = p.y;
+    pos_ref[2 * n + dst] = p.z;
   });
+}
+
+// Steps 1 to 4 in one block for small batches (atoms in registers, 4 tiles per wavefront;
+// histogram in LDS): one launch instead of four.  In a replayed graph 256 atoms take 6.3 us and 12.1
+// by the four launches, 864 atoms 7.6 and 13.5, 2048 11.9 and 13.9, 2916 14.9 and 13.8, 4000 17.7
+// and 13.2; a call that finds nothing to do (MD_IF_FLAGGED) costs 4.7 us per launch.  Hence up to
+// 32 tiles, and up to 64 where the rebuild is conditional.
+constexpr int SMALL_TILES = 64, SMALL_TILES_ALWAYS = 32, SMALL_CELLS = 4096;
+__global__ __launch_bounds__(1024) void k_bin_small(md_batch b, int mode, double4* pos,
+                                                    double* vel, int* id, double* pos_ref,
+                                                    int* cell_start, md_ctl_dev* ctl) {
+  constexpr int TW = SMALL_TILES / 16;  // tiles per wavefront
+  __shared__ int s_cell[SMALL_CELLS];   // counts, then first slots
+  __shared__ int s_id[SMALL_TILES * MD_WAVE];
+  __shared__ int s_w[17];
+  const bool go = mode == MD_ALWAYS || md_displacement_exceeded(ctl);
+  if (threadIdx.x == 0) ctl->rebuild = go ? 1 : 0;
+  if (!go) return;
+  const int n = b.n_atoms, n_cells = b.n_cells;
+  const int w = threadIdx.x / MD_WAVE, lane = threadIdx.x & (MD_WAVE - 1);
+  for (int k = threadIdx.x; k < n_cells; k += 1024) s_cell[k] = 0;
+  __syncthreads();
+  double4 p[TW];
+  double v[TW][3];
+  int my[TW], cell[TW], slot[TW], bad = 0;
+#pragma unroll
+  for (int u = 0; u < TW; ++u) {
+    const int t = w + 16 * u;
+    cell[u] = -1;
+    if (t >= b.n_tiles) continue;
+    const md_tile T = b.tiles[t];
+    if (lane >= T.count) continue;
+    const int i = T.first + lane;
+    p[u] = pos[i];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) v[u][q] = vel[q * n + i];
+    my[u] = id[i];
+    cell[u] = wrap_and_cell(b.domains[T.rep], p[u], bad);
+    slot[u] = atomicAdd(&s_cell[cell[u]], 1);
+  }
+  if (bad) md_flag(ctl, bad);
+  __syncthreads();
+  // exclusive scan: a run of cells per thread
+  const int per = (n_cells + 1023) / 1024;
+  const int beg = min(n_cells, (int)threadIdx.x * per), end = min(n_cells, beg + per);
+  int mine = 0, total;
+  for (int k = beg; k < end; ++k) mine += s_cell[k];
+  int run = block_incl_scan(mine, s_w, total) - mine;
+  for (int k = beg; k < end; ++k) {
+    const int c = s_cell[k];
+    s_cell[k] = run;
+    cell_start[k] = run;
+    run += c;
+  }
+  if (threadIdx.x == 0) {
+    cell_start[n_cells] = total;
+    ctl->n_rebuilds += 1;
+    ctl->n_dmax = 0;      // displacements now measured afresh
+    ctl->rec_stale = 1;   // atoms reordered: carried-over neighbour records are void
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < TW; ++u)
+    if (cell[u] >= 0) s_id[s_cell[cell[u]] + slot[u]] = my[u];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < TW; ++u) {
+    if (cell[u] < 0) continue;
+    const int first = s_cell[cell[u]], last = cell[u] + 1 < n_cells ? s_cell[cell[u] + 1] : total;
+    int dst = first;  // ids are unique: the rank by id is a permutation of the segment
+    for (int k = first; k < last; ++k) dst += s_id[k] < my[u];
+    pos[dst] = p[u];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) vel[q * n + dst] = v[u][q];
+    id[dst] = my[u];
+    pos_ref[dst] = p[u].x;
+    pos_ref[n + dst] = p[u].y;
+    pos_ref[2 * n + dst] = p[u].z;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -806,13 +896,20 @@ extern "C" int md_bin_cells(const md_batch* b, md_rebuild_mode mode, double* pos
   int* id_s = (int*)(w + L.id_s);
   md_ctl_dev* c = (md_ctl_dev*)ctl;
   hipStream_t st = (hipStream_t)stream;
+  if (b->n_tiles <= (mode == MD_ALWAYS ? SMALL_TILES_ALWAYS : SMALL_TILES) &&
+      b->n_cells <= SMALL_CELLS) {
+    MD_LAUNCH_TIMED(MD_KERNEL_BIN_COUNT, k_bin_small, dim3(1), dim3(1024), 0, st, *b, (int)mode,
+                    (double4*)pos, vel, id, pos_ref, cell_start, c);
+    MD_LAUNCH_CHECK();
+    return MD_OK;
+  }
   const dim3 grid(md_atom_grid(b->n_tiles)), block(MD_ATOM_BLOCK);
   MD_LAUNCH_TIMED(MD_KERNEL_BIN_COUNT, k_bin_count, grid, block, 0, st, *b, (int)mode,
-                  (double4*)pos, cell_of, rank_of, counts, c);
+                  (const double4*)pos, vel, id, cell_of, rank_of, counts, pos_s, vel_s, id_s, c);
   MD_LAUNCH_CHECK();
-  if (b->n_cells <= MD_SCAN_ONE_MAX) {
-    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, st, b->n_cells, (int)mode, counts,
-                       cell_start, c);
+  if (b->n_cells <= MD_SCAN_DIRECT_MAX) {
+    hipLaunchKernelGGL(k_scan_direct, dim3((b->n_cells + 1023) / 1024), dim3(1024), 0, st,
+                       b->n_cells, (int)mode, counts, cell_start, c);
     MD_LAUNCH_CHECK();
   } else {
     const int nb = std::min(MD_SCAN_BLOCKS, (b->n_cells + 1023) / 1024);
@@ -829,13 +926,10 @@ extern "C" int md_bin_cells(const md_batch* b, md_rebuild_mode mode, double* pos
     MD_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(k_bin_scatter, grid, block, 0, st, *b, (int)mode, cell_of, rank_of,
-                     cell_start, id, src, sid, c);
+                     cell_start, id_s, src, sid, counts, c);
   MD_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_bin_gather, grid, block, 0, st, *b, (int)mode, cell_of, cell_start, src,
-                     sid, (const double4*)pos, vel, pos_s, vel_s, id_s, c);
-  MD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_bin_copyback, grid, block, 0, st, *b, (int)mode, pos_s, vel_s, id_s,
-                     (double4*)pos, vel, id, pos_ref, c);
+                     sid, pos_s, vel_s, (double4*)pos, vel, id, pos_ref, c);
   MD_LAUNCH_CHECK();
   return MD_OK;
 }
