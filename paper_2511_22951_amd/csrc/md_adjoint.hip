@@ -12,7 +12,7 @@
 //   dD/dc_F_k   = sum_i beta_k'(rhobar_i) tau_i
 // The F'' and beta' terms are the mixed second derivatives.
 //
-// One kernel visits each atom's list twice (the second visit needs the complete
+// A kernel visits each atom's list twice (the second visit needs the complete
 // tau_i); where the density Jacobian sum_j beta_k(r_ij) = d rhobar_i / d c_rho_k of
 // the fixed positions is kept, the second visit is a product with its rows instead.
 // The same file holds that Jacobian's kernel and the force-matching loss.  Each
@@ -33,6 +33,8 @@ namespace {
 #define MD_ADJ_COPIES 8   // most copies of the phi and rho bins per wavefront
 #define MD_ADJ_COPIES_JAC 4  // the same with the density Jacobian (fewer adds per pair)
 #define MD_ADJ_LDS 49152  // LDS per block that the copies may fill
+#define MD_ROWS_MAX_COEF 128 // k_eam_adjoint_rows: coefficients per function
+#define MD_ROWS_LDS 81920     // and LDS per block
 #define MD_JAC_MAX_COEF 128  // density Jacobian: rows of 64 atoms in LDS (64 KiB)
 
 __device__ __forceinline__ void bspline_basis(double t, double b[4], double g[4]) {
@@ -282,6 +284,176 @@ __global__ __launch_bounds__(64 * LANES) void k_eam_adjoint(
   }
 }
 
+// The same gradient by per-atom rows in LDS, h_i[k] = sum_j w_ij 2 beta'_k(t_ij) / h over i's
+// pairs: phi's bins are sums of the rows, rho's first term their sums weighted with F'_i, and
+// tau_i is the product of the row with rho's coefficients -- four LDS adds per pair instead of
+// eight and four reads.  An atom's row takes adds of its own lanes only, all in one wavefront.
+// After the visit wave w contracts the rows of atoms w, w + waves, ..., lane k column k.
+// Without the density Jacobian the rows are then made again of beta_k(r_ij).
+//
+// 512,000 atoms (1024 boxes), 64 coefficients, with the Jacobian: 205 us, 248 by the bins of
+// k_eam_adjoint (LDS pipe 57 % busy, texture-data path 90 %: now bound by the gathers of six
+// doubles per pair; four blocks of 35 KB per CU).  One entry in flight per lane 270 us, four 226
+// (94 registers).  At 2 lanes and 1 a block has only two wavefronts or one beside its rows: those
+// take k_eam_adjoint, as do splines of more coefficients than two such blocks per CU hold.
+template <int LANES, int U, bool JAC>
+__global__ __launch_bounds__(64 * LANES) void k_eam_adjoint_rows(
+    md_batch b, const double4* __restrict__ pos, const int* __restrict__ neigh,
+    const int* __restrict__ nneigh, int npad, const double* __restrict__ saved,
+    const double* __restrict__ jac, const double* __restrict__ G, AdjGeom g, double rc2,
+    double* tile_bins, md_ctl_dev* ctl) {
+  // LDS: rows [64][stride] (later the waves' sums), rho coefficients, F' and -F'' tau of the
+  // tile's atoms, F bins [waves][n_emb]
+  extern __shared__ double rows[];
+  const int nw = LANES, wid = threadIdx.x / MD_WAVE, lane = threadIdx.x & (MD_WAVE - 1);
+  double* c_rho = rows + (size_t)MD_TILE * g.stride;
+  double* s_fp = c_rho + g.n_rho;
+  double* s_w = s_fp + MD_TILE;
+  double* emb_bins = s_w + MD_TILE;
+  const int t = md_remap_block(b.n_tiles);
+  if (t >= b.n_tiles) return;
+  for (int q = threadIdx.x; q < MD_TILE * g.stride; q += blockDim.x) rows[q] = 0.0;
+  for (int q = threadIdx.x; q < nw * g.n_emb; q += blockDim.x) emb_bins[q] = 0.0;
+  for (int q = threadIdx.x; q < g.n_rho; q += blockDim.x) c_rho[q] = g.c_rho[q];
+  __syncthreads();
+  const md_tile T = b.tiles[t];
+  const md_domain& Dm = b.domains[T.rep];
+  // minimum image: a non-periodic axis gets 0 as inverse length (its shift is 0)
+  const double len[3] = {Dm.len[0], Dm.len[1], Dm.len[2]};
+  const double inv[3] = {Dm.periodic[0] ? Dm.inv_len[0] : 0.0,
+                         Dm.periodic[1] ? Dm.inv_len[1] : 0.0,
+                         Dm.periodic[2] ? Dm.inv_len[2] : 0.0};
+  const int a = threadIdx.x / LANES, l = threadIdx.x % LANES;
+  const int n = b.n_atoms;
+  const bool mine = a < T.count;
+  const int i = T.first + min(a, T.count - 1);
+  const int nn = mine ? nneigh[i] & MD_NN_MASK : 0;
+  const int cnt = nn > l ? (nn - l + LANES - 1) / LANES : 0;
+  const size_t stride = (size_t)npad * LANES;
+  const int* nb = neigh + (size_t)i * LANES + l;
+  const double4 pi = pos[i];
+  double* row = rows + (size_t)a * g.stride;
+  double umin = 0.0, umax = 0.0;
+  {
+    const double gix = G[i], giy = G[n + i], giz = G[2 * n + i];
+    adj_visit<U>(
+        nb, stride, cnt, i,
+        [&](int j) {
+          const double4 p = pos[j];
+          return AdjRec1{p.x, p.y, p.z, G[j], G[n + j], G[2 * n + j]};
+        },
+        [&](const AdjRec1& q) {
+          double d[3];
+          const double r2 = pair_disp2(pi, q.x, q.y, q.z, len, inv, d);
+          if (!(r2 < rc2)) return;
+          const double ir = rsqrt_nr(r2);
+          const double u = (r2 * ir - g.r_lo) * g.r_inv_h;
+          umin = fmin(umin, u);
+          umax = fmax(umax, u);
+          double tt;
+          const int k = interval_u(u, g.nr, tt);
+          const double w = fma(gix - q.gx, d[0], fma(giy - q.gy, d[1], (giz - q.gz) * d[2])) * ir;
+          const double t2 = tt * tt, s = 1.0 - tt;
+          atomicAdd(&row[k], -(s * s) * w);
+          atomicAdd(&row[k + 1], tt * fma(3.0, tt, -4.0) * w);
+          atomicAdd(&row[k + 2], fma(-3.0, t2, fma(2.0, tt, 1.0)) * w);
+          atomicAdd(&row[k + 3], t2 * w);
+        });
+  }
+  bool oor = umin < 0.0 || umax > (double)g.nr;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  // tau_i = sum_j rho'(r_ij) s_ij
+  double dr = 0.0;
+  for (int k = l; k < g.n_rho; k += LANES) dr = fma(c_rho[k], row[k], dr);
+  const double tau = -0.5 * g.r_inv_h * md_group_sum<LANES>(dr);
+  if (l == 0) {
+    s_fp[a] = mine ? saved[n + i] : 0.0;
+    s_w[a] = mine ? -saved[2 * n + i] * tau : 0.0;
+    if (mine) {
+      double tt, bb[4], gg[4];
+      const int k = interval(saved[i], g.e_lo, g.e_inv_h, g.ne, tt, oor);
+      bspline_basis(tt, bb, gg);
+      double* b_emb = emb_bins + (size_t)wid * g.n_emb;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) atomicAdd(&b_emb[k + q], -gg[q] * g.e_inv_h * tau);
+    }
+  }
+  if (__any(oor)) {
+    if (lane == 0) md_flag(ctl, MD_FLAG_TABLE_RANGE);
+  }
+  __syncthreads();
+  constexpr int KW = (MD_ROWS_MAX_COEF + MD_WAVE - 1) / MD_WAVE;  // columns per lane
+  double s_phi[KW], s_rho[KW];
+#pragma unroll
+  for (int c = 0; c < KW; ++c) {
+    const int k = lane + c * MD_WAVE;
+    double h = 0.0, hf = 0.0, f2 = 0.0;
+    if (k < g.n_rho) {
+#pragma unroll 4
+      for (int q = wid; q < T.count; q += nw) {
+        const double v = rows[(size_t)q * g.stride + k];
+        if (JAC)
+          f2 = fma(s_w[q], __builtin_nontemporal_load(jac + (size_t)(T.first + q) * g.n_rho + k),
+                   f2);
+        h += v;
+        hf = fma(s_fp[q], v, hf);
+      }
+    }
+    s_phi[c] = 0.25 * g.r_inv_h * h;
+    s_rho[c] = fma(0.5 * g.r_inv_h, hf, f2);
+  }
+  __syncthreads();
+  if (!JAC) {
+    for (int q = threadIdx.x; q < MD_TILE * g.stride; q += blockDim.x) rows[q] = 0.0;
+    __syncthreads();
+    adj_visit<U>(
+        nb, stride, cnt, i,
+        [&](int j) {
+          const double4 p = pos[j];
+          return make_double3(p.x, p.y, p.z);
+        },
+        [&](const double3& q) {
+          double d[3];
+          const double r2 = pair_disp2(pi, q.x, q.y, q.z, len, inv, d);
+          if (!(r2 < rc2)) return;
+          double tt, bb[4];
+          const int k = interval_u((r2 * rsqrt_nr(r2) - g.r_lo) * g.r_inv_h, g.nr, tt);
+          basis6(tt, bb);
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) atomicAdd(&row[k + q4], bb[q4]);
+        });
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < KW; ++c) {
+      const int k = lane + c * MD_WAVE;
+      double f2 = 0.0;
+      if (k < g.n_rho)
+        for (int q = wid; q < T.count; q += nw) f2 = fma(s_w[q], rows[(size_t)q * g.stride + k], f2);
+      s_rho[c] = fma(f2, 1.0 / 6.0, s_rho[c]);
+    }
+    __syncthreads();
+  }
+  // the waves' sums, in wave order
+  double* part = rows;  // [waves][n_phi + n_rho]
+  const int n_hot = g.n_phi + g.n_rho;
+#pragma unroll
+  for (int c = 0; c < KW; ++c) {
+    const int k = lane + c * MD_WAVE;
+    if (k < g.n_rho) {
+      part[wid * n_hot + k] = s_phi[c];
+      part[wid * n_hot + g.n_phi + k] = s_rho[c];
+    }
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < g.n_bins; q += blockDim.x) {
+    double s = 0.0;
+    for (int w = 0; w < nw; ++w)
+      s += q < n_hot ? part[w * n_hot + q] : emb_bins[(size_t)w * g.n_emb + q - n_hot];
+    tile_bins[(size_t)q * b.n_tiles + t] = s;
+  }
+}
+
 // grad[q] = sum over tiles of the tile partials tile_bins[q][tile] (bin-major, so one
 // block reads one contiguous row): thread h adds tiles h, h + 256, ... in order and
 // the block's threads are combined in a fixed tree.
@@ -456,10 +628,35 @@ int backward(const md_batch* b, const md_eam* p, md_precision prec, const double
     auto lds_of = [&](int c) {
       return ((size_t)nw * ((size_t)c * g.stride + g.n_emb) + g.n_rho + extra) * sizeof(double);
     };
-    g.copies = jac ? MD_ADJ_COPIES_JAC : MD_ADJ_COPIES;
-    while (g.copies > 1 && lds_of(g.copies) > MD_ADJ_LDS) g.copies >>= 1;
-    const size_t lds = lds_of(g.copies);
-    if (lds > 65536) return MD_ERR_ARG;  // fewer lanes per atom, or fewer coefficients
+    if (lds_of(1) > 65536) return MD_ERR_ARG;  // fewer lanes per atom, or fewer coefficients
+    // rows: two blocks of a tile's 64 atoms share a CU (and a block has four wavefronts or more)
+    const int row = g.n_rho | 1;  // an odd number of doubles: equal columns on different banks
+    const size_t row_lds =
+        ((size_t)MD_TILE * (row + 2) + g.n_rho + (size_t)nw * g.n_emb) * sizeof(double);
+    if (L >= 4 && g.n_rho <= MD_ROWS_MAX_COEF && nw * n_hot <= MD_TILE * row &&
+        row_lds <= MD_ROWS_LDS) {
+      g.stride = row;
+#define MD_ADJ_ROWS(LN, J)                                                                     \
+  MD_LAUNCH_TIMED(MD_KERNEL_EAM_ADJOINT, (k_eam_adjoint_rows<LN, MD_ADJ_U, J>), grid, block,    \
+                  row_lds, st, *b, (const double4*)pos, nl->neigh, nl->nneigh, npad, saved, jac, \
+                  grad_force, g, rc2, tile_bins, (md_ctl_dev*)ctl)
+#define MD_ADJ_ROWS_L(J)                \
+  switch (L) {                          \
+    case 4: MD_ADJ_ROWS(4, J); break;   \
+    case 8: MD_ADJ_ROWS(8, J); break;   \
+    default: MD_ADJ_ROWS(16, J); break; \
+  }
+      if (jac) {
+        MD_ADJ_ROWS_L(true);
+      } else {
+        MD_ADJ_ROWS_L(false);
+      }
+#undef MD_ADJ_ROWS_L
+#undef MD_ADJ_ROWS
+    } else {
+      g.copies = jac ? MD_ADJ_COPIES_JAC : MD_ADJ_COPIES;
+      while (g.copies > 1 && lds_of(g.copies) > MD_ADJ_LDS) g.copies >>= 1;
+      const size_t lds = lds_of(g.copies);
 #define MD_ADJ_LAUNCH(LN, J)                                                                   \
   MD_LAUNCH_TIMED(MD_KERNEL_EAM_ADJOINT, (k_eam_adjoint<LN, MD_ADJ_U, J>), grid, block, lds,    \
                   st, *b, (const double4*)pos, nl->neigh, nl->nneigh, npad, saved, jac,         \
@@ -472,13 +669,14 @@ int backward(const md_batch* b, const md_eam* p, md_precision prec, const double
     case 8: MD_ADJ_LAUNCH(8, J); break;   \
     default: MD_ADJ_LAUNCH(16, J); break; \
   }
-    if (jac) {
-      MD_ADJ_LAUNCH_L(true);
-    } else {
-      MD_ADJ_LAUNCH_L(false);
-    }
+      if (jac) {
+        MD_ADJ_LAUNCH_L(true);
+      } else {
+        MD_ADJ_LAUNCH_L(false);
+      }
 #undef MD_ADJ_LAUNCH_L
 #undef MD_ADJ_LAUNCH
+    }
     MD_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(k_adj_reduce, dim3(g.n_bins), dim3(256), 0, st, tile_bins, b->n_tiles,

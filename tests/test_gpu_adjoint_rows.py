@@ -1,0 +1,80 @@
+"""The adjoint by per-atom rows (4 lanes per atom and more, coefficients that fit) against the
+adjoint by bins (2 lanes, the same snapshots): coefficient counts of the smallest splines, around
+one and two columns per lane and past the rows' limit, with and without the density Jacobian,
+tiles full and with remainders.  Both sum the same terms in FP64 in different orders: within
+1e-12 of the largest entry of each function's gradient.  The LJ pass with a list addressed with 64
+bits (streamed) against the same list in 32 bits: the same bits."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+
+import mdinputs as mi
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _snapshots():
+    rng = np.random.default_rng(21)
+    out = []
+    for cells in ((4, 4, 4), (5, 5, 5), (4, 4, 5)):
+        pos, box = mi.fcc_lattice(*cells, 3.7)
+        out.append(SimpleNamespace(pos=mi.wrap_into_box(pos + rng.normal(0, 0.08, pos.shape), box),
+                                   box=box))
+    return out
+
+
+def _potential(n):
+    from paper_2511_22951_amd import md
+    r_lo, r_cut = 1.5, 5.5
+    r = r_lo + (np.arange(n) - 1) * (r_cut - r_lo) / (n - 3)
+    e = (np.arange(n) - 1) * 4.0 / (n - 3)
+    return md.EAMPotential(np.exp(-2.0 * r) - 0.1 * np.exp(-r), np.exp(-r), 0.1 * e * e - e, r_lo,
+                           (r_cut - r_lo) / (n - 3), 0.0, 4.0 / (n - 3), r_cut)
+
+
+@pytest.mark.parametrize("jac", [False, True])
+@pytest.mark.parametrize("n", [6, 7, 63, 64, 65, 100, 128, 129, 300])
+def test_gradient_by_rows(n, jac):
+    from paper_2511_22951_amd import fm
+    snaps, pot = _snapshots(), _potential(n)
+    rng = np.random.default_rng(n)
+    cot = [rng.normal(size=s.pos.shape) for s in snaps]
+    grads = {}
+    for lanes in (2, 4, 8, 16):
+        batch = fm.SnapshotBatch(snaps, 5.8, lanes=lanes, density_jacobian=jac)
+        batch.forces(pot)
+        try:
+            g = batch.backward(pot, batch.to_current_order(np.concatenate(cot)))
+        except Exception as err:  # the bins of many waves do not fit: refused, as ever
+            assert lanes > 4 and n > 128 and "status -1" in str(err)
+            continue
+        batch.state.check_flags()
+        grads[lanes] = g.cpu().numpy()
+    assert 4 in grads
+    for lanes, g in grads.items():
+        for k in range(3):
+            want = grads[2][k * n:(k + 1) * n]
+            scale = np.max(np.abs(want))
+            assert scale > 0.0
+            assert np.max(np.abs(g[k * n:(k + 1) * n] - want)) <= 1e-12 * scale, (lanes, k)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("lanes", [1, 4])
+def test_lj_streamed_list(lanes, prec):
+    from paper_2511_22951_amd import md
+    pos, box = mi.fcc_lattice(8, 8, 8, 5.26)
+    pos = mi.wrap_into_box(pos + np.random.default_rng(2).normal(0, 0.1, pos.shape), box)
+    plan = md.Plan([box], [len(pos)], 8.8)
+    out = []
+    for max_neigh in (128, 65536):  # 2^18 and 2^27 entries
+        st = md.State(plan, pos, None, prec)
+        nl = md.NeighborList(plan.n_atoms, max_neigh, lanes)
+        md.md_bin_cells(st)
+        md.md_build_neighbors(st, nl)
+        md.md_lj_forces(st, md.lj_params(0.0104, 3.4, 8.5), nl)
+        st.check_flags()
+        out.append(st.force.clone())
+    assert torch.equal(out[0], out[1]) and float(out[0].abs().max()) > 0
