@@ -287,6 +287,12 @@ __device__ __forceinline__ int load_idx(const int* neigh, uint32_t e) {
   return *reinterpret_cast<const int*>(reinterpret_cast<const char*>(neigh) + (e << 2));
 }
 __device__ __forceinline__ int load_idx(const int* neigh, uint64_t e) { return neigh[e]; }
+// The LJ pass reads its list once a step: where it is addressed with 64 bits (far larger than the
+// last-level cache) it is streamed past the caches, so that the records stay in them.
+__device__ __forceinline__ int load_once(const int* neigh, uint32_t e) { return load_idx(neigh, e); }
+__device__ __forceinline__ int load_once(const int* neigh, uint64_t e) {
+  return __builtin_nontemporal_load(neigh + e);
+}
 
 // Visit the nn list entries of one atom handled by lane l of LANES: entry m sits
 // at element ((m / LANES) * npad + i) * LANES + l, i.e. e0 + (m / LANES) * stride.
@@ -299,7 +305,7 @@ __device__ __forceinline__ void visit_list(const int* neigh, E e0, E stride, int
   for (; m + (U - 1) * LANES < nn; m += U * LANES) {
     int j[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) j[u] = load_idx(neigh, e + u * stride);
+    for (int u = 0; u < U; ++u) j[u] = load_once(neigh, e + u * stride);
     e += U * stride;
     decltype(load(0)) q[U];
 #pragma unroll
@@ -307,7 +313,7 @@ __device__ __forceinline__ void visit_list(const int* neigh, E e0, E stride, int
 #pragma unroll
     for (int u = 0; u < U; ++u) pair(q[u]);
   }
-  for (; m < nn; m += LANES, e += stride) pair(load(load_idx(neigh, e)));
+  for (; m < nn; m += LANES, e += stride) pair(load(load_once(neigh, e)));
 }
 
 // Software-pipelined variant for the EAM passes: the list indices of the next U
@@ -1085,8 +1091,6 @@ int launch_eam(const md_batch& b, const md_eam& p, const char* tab, const md_tab
   g.q_lo = qg.q_lo;
   g.q_inv_h = 1.0 / qg.h;
   const R rc2 = (R)(p.r_cut * p.r_cut);
-  const int bt = block_threads(nl, b.n_tiles), TPB = bt / (64 * LANES);
-  const dim3 grid(md_grid_blocks((b.n_tiles + TPB - 1) / TPB)), block(bt);
   const int npad = md_npad(b.n_atoms);
   const R* rtab = (const R*)(tab + TL.rtab);
   const R* ftab = (const R*)(tab + TL.ftab);
@@ -1095,6 +1099,14 @@ int launch_eam(const md_batch& b, const md_eam& p, const char* tab, const md_tab
   const bool ld = table_in_lds<R>(rows, MD_RTAB_W);
   const size_t lds_d = ld ? (size_t)rows * MD_RTAB_W * sizeof(R) : 0;
   const size_t lds_f = ld ? (size_t)rows * MD_FTAB_W * sizeof(R) : 0;
+  // tables that take no time to stage (coarse splines): the smallest workgroups, which wait less
+  // for their slowest wavefront (512,000 atoms, FP64, 61 intervals: both passes 224-228 us with
+  // 1024 threads, 219 with 512, 220 with 256; forces from the density Jacobian 171, 167, 166).
+  // Fused drifts keep block_threads' choice, which their displacement slots are checked for.
+  int bt = block_threads(nl, b.n_tiles);
+  if (!nl.block && ld && lds_d <= 16384 && !dr.pos_out) bt = std::max(256, 64 * LANES);
+  const int TPB = bt / (64 * LANES);
+  const dim3 grid(md_grid_blocks((b.n_tiles + TPB - 1) / TPB)), block(bt);
 #define MD_EAM_LAUNCH(EVB, TL_, E_, TH_)                                                          \
   do {                                                                                         \
     if (jac) {                                                                                 \
@@ -1181,7 +1193,10 @@ void launch_lj(const md_batch& b, const md_lj& p, const double* pos, const md_nl
   const int bt = block_threads(nl, b.n_tiles), TPB = bt / (64 * LANES);
   const dim3 grid(md_grid_blocks((b.n_tiles + TPB - 1) / TPB)), block(bt);
   const int npad = md_npad(b.n_atoms);
-  const bool big = md_big_list(nl, npad);
+  // lists beyond twice the 256 MB last-level cache too, to stream them (load_once): 2,048,000
+  // atoms 349 -> 340 us.  (The EAM passes' are read twice a step and gain by the caches: 640,000
+  // atoms 143 us, streamed 164.)
+  const bool big = (size_t)nl.max_neigh * npad >= ((size_t)1 << 27);
 #define MD_LJ_LAUNCH2(EVB, E_, TH_)                                                            \
   MD_LAUNCH_TIMED(MD_KERNEL_LJ, (k_lj<R, LANES, EVB, E_, TH_>), grid, block, 0, st, b,        \
                   (const double4*)pos, nl.neigh, nl.nneigh, npad, c, rc2, (R*)force, vel,      \
