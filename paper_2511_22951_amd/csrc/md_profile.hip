@@ -148,16 +148,19 @@ __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_obs_eam_w(md_batch b, md_eam 
 // The EAM passes on lists of LANES lanes per atom, with the phi and rho coefficients (one grid)
 // staged in LDS as pairs {rho, phi}: the four a pair of atoms needs are four 16-byte LDS reads.
 // A wavefront takes 64 / LANES atoms of a tile, lane l of an atom its entries l, l + LANES, ..
-// (a coalesced read of the list), four in flight; blocks stride over the batch, so that the
-// staging is paid a few times per CU.
+// (a coalesced read of the list); blocks stride over the batch, so that the staging is paid
+// twice per CU.
 //
-// Bound by the neighbours' gathers (the texture-data path is 98 % busy; VALU 38 %).  640,000 Al
-// atoms, lists of four lanes: 264 us and 287 us for the two passes, against 379 and 413 with an
-// atom per lane and coefficients through the caches (eight more divergent loads per pair).
-// Holding the kernels to 80 registers (six wavefronts per SIMD) spills: 317 and 621 us.
-constexpr int OBS_BLOCK = 512;
+// Bound by the neighbours' gathers, which wait for one another: one neighbour in flight per lane
+// and 24 wavefronts per CU in two large blocks of neighbouring atoms are the best.  640,000 Al
+// atoms, lists of four lanes: 190 us and 206 us for the two passes (379 and 413 with an atom per
+// lane and coefficients through the caches).  Four in flight and 16 wavefronts: 267 and 286;
+// two in flight: 239 and 209 (24 wavefronts), 264 and 283 (16); three blocks of 512 threads: 194
+// and 211; four of 384: 259 and 295; 32 wavefronts: 184 and 257 (12 registers spilled in the
+// second).  A grid of whole rounds matters: 1024 blocks of which 768 are resident took 230 and 250.
+constexpr int OBS_BLOCK = 768;
 constexpr int OBS_MAX_COEF = 4096;  // 64 KiB of LDS
-constexpr int OBS_GRID = 1024;      // four blocks per CU
+constexpr int OBS_GRID = 512;       // two blocks per CU
 
 struct ObsGrid {
   double x_lo, inv_h, h;
@@ -189,27 +192,17 @@ __device__ __forceinline__ double obs_interval(const ObsGrid& G, const double2* 
   return u - f;
 }
 
-// body(pos_j, j) for this lane's entries of the list of atom i.
+// body(load(j)) for this lane's entries of the list of atom i, the next index in flight.
 template <int LANES, typename Load, typename Body>
-__device__ __forceinline__ void obs_visit(const int* nb, size_t stride, int cnt, int self,
-                                          Load load, Body body) {
-  constexpr int U = 4;
+__device__ __forceinline__ void obs_visit(const int* nb, size_t stride, int cnt, Load load,
+                                          Body body) {
   if (cnt <= 0) return;
-  int jn[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) jn[u] = nb[u < cnt ? u * stride : 0];
-  for (int m0 = 0; m0 < cnt; m0 += U) {
-    decltype(load(0)) q[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) q[u] = load(m0 + u < cnt ? jn[u] : self);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int m = m0 + U + u;
-      jn[u] = nb[m < cnt ? m * stride : 0];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (m0 + u < cnt) body(q[u]);
+  int jn = nb[0];
+  for (int m = 0; m < cnt; ++m) {
+    const auto q = load(jn);
+    nb += m + 1 < cnt ? stride : 0;
+    jn = *nb;
+    body(q);
   }
 }
 
@@ -220,7 +213,7 @@ struct ObsRec {
 // PASS 0: rho_fp = {rhobar_i, F'(rhobar_i)}, e_i = F + 1/2 sum phi.  PASS 1: w_i (F' read from
 // rho_fp).  The same formulas as k_obs_eam_rho and k_obs_eam_w.
 template <int LANES, int PASS>
-__global__ __launch_bounds__(OBS_BLOCK) void k_obs_eam(md_batch b, md_eam p, ObsGrid G,
+__global__ __launch_bounds__(OBS_BLOCK, 6) void k_obs_eam(md_batch b, md_eam p, ObsGrid G,
                                                        const double4* __restrict__ pos,
                                                        md_nlist nl, size_t npad, double* rho_fp,
                                                        double* out, md_ctl_dev* ctl) {
@@ -250,7 +243,7 @@ __global__ __launch_bounds__(OBS_BLOCK) void k_obs_eam(md_batch b, md_eam p, Obs
     const int cnt = nn > l ? (nn - l + LANES - 1) / LANES : 0;
     double rho = 0.0, phi = 0.0, w[6] = {0, 0, 0, 0, 0, 0};
     obs_visit<LANES>(
-        nl.neigh + (size_t)i * LANES + l, npad * LANES, cnt, i,
+        nl.neigh + (size_t)i * LANES + l, npad * LANES, cnt,
         [&](int j) {
           const double4 q = pos[j];
           return ObsRec{q.x, q.y, q.z, PASS ? fp[j] : 0.0};
