@@ -296,46 +296,26 @@ __device__ __forceinline__ int load_once(const int* neigh, uint64_t e) {
 
 // Visit the nn list entries of one atom handled by lane l of LANES: entry m sits
 // at element ((m / LANES) * npad + i) * LANES + l, i.e. e0 + (m / LANES) * stride.
-// U entries are in flight per lane: indices first, then records, then the math.
-template <int LANES, int U, typename E, typename Load, typename Pair>
-__device__ __forceinline__ void visit_list(const int* neigh, E e0, E stride, int l, int nn,
-                                           Load load, Pair pair) {
-  int m = l;
-  E e = e0;
-  for (; m + (U - 1) * LANES < nn; m += U * LANES) {
-    int j[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) j[u] = load_once(neigh, e + u * stride);
-    e += U * stride;
-    decltype(load(0)) q[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) q[u] = load(j[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) pair(q[u]);
-  }
-  for (; m < nn; m += LANES, e += stride) pair(load(load_once(neigh, e)));
-}
-
-// Software-pipelined variant for the EAM passes: the list indices of the next U
-// entries are loaded while the records of the current U are in flight, so a lane
-// waits for one round trip per U entries instead of two.  All loads are issued
+// The indices of the next U entries are loaded while the records of the current U are in
+// flight, so a lane waits for one round trip per U entries instead of two.  All loads are issued
 // unconditionally in a fixed order (entries past the lane's end read the atom's
 // first entry and are replaced by the atom itself, `self`), so the compiler can
 // wait for the records alone; pair(q, valid) masks the padding.
-template <int LANES, int U, typename E, typename Load, typename Pair>
+template <int LANES, int U, bool ONCE = false, typename E, typename Load, typename Pair>
 __device__ __forceinline__ void visit_list_pipe(const int* neigh, E e0, E stride, int l, int nn,
                                                 int self, Load load, Pair pair) {
   const int cnt = nn > l ? (nn - l + LANES - 1) / LANES : 0;  // this lane's entries
+  auto index = [&](E e) { return ONCE ? load_once(neigh, e) : load_idx(neigh, e); };
   int jn[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) jn[u] = load_idx(neigh, u < cnt ? e0 + u * stride : e0);
+  for (int u = 0; u < U; ++u) jn[u] = index(u < cnt ? e0 + u * stride : e0);
   E e = e0 + U * stride;
   for (int b0 = 0; b0 < cnt; b0 += U) {
     decltype(load(0)) q[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) q[u] = load(b0 + u < cnt ? jn[u] : self);
 #pragma unroll
-    for (int u = 0; u < U; ++u) jn[u] = load_idx(neigh, b0 + U + u < cnt ? e + u * stride : e0);
+    for (int u = 0; u < U; ++u) jn[u] = index(b0 + U + u < cnt ? e + u * stride : e0);
     e += U * stride;
 #pragma unroll
     for (int u = 0; u < U; ++u) pair(q[u], b0 + u < cnt);
@@ -925,6 +905,9 @@ __global__ __launch_bounds__(FBLOCK) void k_lj(
     const int* __restrict__ nneigh, int npad, LJc c, R rc2, R* force, double* vel,
     double inv_mass, double half_dt, DriftArgs dr, const uint4* __restrict__ rec, long long* ev,
     int ev_cap, md_ctl_dev* ctl) {
+  // The gathers set the time (texture-data path 90 % busy).  2,048,000 atoms, FP32 at one lane: 341
+  // us with indices and records loaded in turn, 325 with the next indices in flight (FP64 577 and
+  // 529); two entries at a time 404, one 455, six 323 (FP64 538), eight 349.
   constexpr int U = 4;
   __shared__ double sh[MD_EV_LEN * 16];
   __shared__ double tsum[MD_EV_LEN * 16];
@@ -945,9 +928,9 @@ __global__ __launch_bounds__(FBLOCK) void k_lj(
   }
   const bool wimg = __any(raw & MD_NN_IMG);
   // the pair force, energy and virial from the separation (x, y, z) = r_j - r_i
-  auto lj_pair = [&](R x, R y, R z) {
+  auto lj_pair = [&](R x, R y, R z, bool valid) {
     const R r2 = x * x + y * y + z * z;
-    if (r2 < rc2) {
+    if (valid && r2 < rc2) {
       const R ir2 = (R)1 / r2;
       const R sr2 = sig2 * ir2;
       const R sr6 = sr2 * sr2 * sr2;
@@ -975,23 +958,25 @@ __global__ __launch_bounds__(FBLOCK) void k_lj(
       // wrap-around, one load per neighbour), as in the EAM passes
       const FixBox X = fix_box(b.domains[T.rep], b.r_ns);
       const uint4 ri = rec[i];
-      visit_list<LANES, U>(neigh, e0, stride, S.l, nn, [&](int j) { return load_rec16(rec, j); },
-                           [&](uint4 q) {
-                             float x, y, z;
-                             fix_sep<false>(q, ri, X, x, y, z);
-                             lj_pair(x, y, z);
-                           });
+      visit_list_pipe<LANES, U, true>(neigh, e0, stride, S.l, nn, i,
+                                [&](int j) { return load_rec16(rec, j); },
+                                [&](uint4 q, bool valid) {
+                                  float x, y, z;
+                                  fix_sep<false>(q, ri, X, x, y, z);
+                                  lj_pair(x, y, z, valid);
+                                });
     } else {
       const Img D(&b.domains[T.rep]);
       const double4 pi = pos[i];
       auto run = [&](auto img_tag) {
         constexpr bool IMG = decltype(img_tag)::value;
-        visit_list<LANES, U>(neigh, e0, stride, S.l, nn,
-                             [&](int j) { return load_rec(pos, j); }, [&](double4 pj) {
-                               Sep sh;
-                               const Sep d = separation<IMG>(D, pj, pi, sh);
-                               lj_pair(d.x, d.y, d.z);
-                             });
+        visit_list_pipe<LANES, U, true>(neigh, e0, stride, S.l, nn, i,
+                                  [&](int j) { return load_rec(pos, j); },
+                                  [&](double4 pj, bool valid) {
+                                    Sep sh;
+                                    const Sep d = separation<IMG>(D, pj, pi, sh);
+                                    lj_pair(d.x, d.y, d.z, valid);
+                                  });
       };
       if (wimg) run(std::true_type{});
       else run(std::false_type{});
@@ -1194,7 +1179,7 @@ void launch_lj(const md_batch& b, const md_lj& p, const double* pos, const md_nl
   const dim3 grid(md_grid_blocks((b.n_tiles + TPB - 1) / TPB)), block(bt);
   const int npad = md_npad(b.n_atoms);
   // lists beyond twice the 256 MB last-level cache too, to stream them (load_once): 2,048,000
-  // atoms 349 -> 340 us.  (The EAM passes' are read twice a step and gain by the caches: 640,000
+  // atoms 349 -> 340 us (before the pass had its indices in flight).  (The EAM passes' are read twice a step and gain by the caches: 640,000
   // atoms 143 us, streamed 164.)
   const bool big = (size_t)nl.max_neigh * npad >= ((size_t)1 << 27);
 #define MD_LJ_LAUNCH2(EVB, E_, TH_)                                                            \
