@@ -18,9 +18,9 @@
 // powering loop otherwise), cutoff functions of R_jk as polynomials in R_jk^2 (no square root,
 // sine or division per pair), pairs enumerated so that the lanes of one step meet different
 // neighbours (their LDS sums do not serialise), wave-uniform loop bounds (the accumulators stay
-// in place).  51 functions, forces and energies: 32,000 Cu atoms 1.37 ms (5.32 ms with the pairs
-// by triangle rows, library exponentials and the network inside the first pass); 864 atoms 0.107
-// ms (4.13 ms with a whole tile of 64 atoms per block, which left all but 14 CUs idle).
+// in place).  51 functions, forces and energies: 32,000 Cu atoms 1.24 ms (5.33 ms with the pairs
+// by triangle rows, library exponentials and the network inside the first pass); 864 atoms 0.100
+// ms (4.12 ms with a whole tile of 64 atoms per block, which left all but 14 CUs idle).
 #include <math.h>
 
 #include <type_traits>
@@ -748,7 +748,7 @@ __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bpnn_kick(md_batch b, const d
 // the evaluation can represent: every zeta a power of two with at most NL distinct values, and
 // |eta| small enough for the exponential table's Taylor factor, |eta| 3 r_c^2 / (2 NT) <= X_MAX
 // (|eta| r_c^2 <= 4.2).  Wherever it holds it is the faster one: 32,000 Cu atoms 1.37 ms against
-// 2.48 ms for the general form (48 functions with one zeta of 3 in place of 4), 864 atoms 0.107
+// 2.48 ms for the general form (48 functions with one zeta of 3 in place of 4), 864 atoms 0.100
 // against 0.165 ms.
 void fast_grid(BpnnDev* d) {
   int lev[NZ], nlev = 0;  // distinct zeta, ascending

@@ -62,7 +62,8 @@ def timed_graph_plan(n_steps, rebuild_every, fused, graph_steps):
 
 def fused_grid_fits(n_tiles, lanes, block=0):
     """Whether a force pass of `lanes` lanes per atom over n_tiles tiles (block / (64 lanes)
-    tiles per block of `block` threads, default 1024; the grid rounded up to a multiple of 8)
+    tiles per block of `block` threads; 0 is 1024 wherever the grid is large; the grid rounded up
+    to a multiple of 8)
     fits the displacement slots the fused kick-drift publishes into."""
     tpb = max(1, (block or 1024) // (64 * lanes))
     blocks = (n_tiles + tpb - 1) // tpb

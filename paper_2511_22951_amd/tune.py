@@ -133,6 +133,6 @@ def best_shape(system, prec, candidates=None, samples=10, use_cache=True, fits=N
 
 
 def best_lanes(system, prec, candidates=CANDIDATES, samples=10, use_cache=True):
-    """Lanes per atom alone (default workgroups of 1024 threads)."""
+    """Lanes per atom alone (workgroups of 1024 threads)."""
     return best_shape(system, prec, [s for s in shapes(prec, candidates, (1024,))], samples,
                       use_cache)[0]
