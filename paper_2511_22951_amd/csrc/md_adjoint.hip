@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64 * LANES) void k_eam_adjoint(
 // After the visit wave w contracts the rows of atoms w, w + waves, ..., lane k column k.
 // Without the density Jacobian the rows are then made again of beta_k(r_ij).
 //
-// 512,000 atoms (1024 boxes), 64 coefficients, with the Jacobian: 205 us, 248 by the bins of
+// 512,000 atoms (1024 boxes), 64 coefficients, with the Jacobian: 210 us, 248 by the bins of
 // k_eam_adjoint (LDS pipe 57 % busy, texture-data path 90 %: now bound by the gathers of six
 // doubles per pair; four blocks of 35 KB per CU).  One entry in flight per lane 270 us, four 226
 // (94 registers).  At 2 lanes and 1 a block has only two wavefronts or one beside its rows: those
@@ -365,7 +365,8 @@ __global__ __launch_bounds__(64 * LANES) void k_eam_adjoint_rows(
   __builtin_amdgcn_wave_barrier();
   // tau_i = sum_j rho'(r_ij) s_ij
   double dr = 0.0;
-  for (int k = l; k < g.n_rho; k += LANES) dr = fma(c_rho[k], row[k], dr);
+  // (columns without a pair are left out, whatever their coefficients hold)
+  for (int k = l; k < g.n_rho; k += LANES) dr = row[k] != 0.0 ? fma(c_rho[k], row[k], dr) : dr;
   const double tau = -0.5 * g.r_inv_h * md_group_sum<LANES>(dr);
   if (l == 0) {
     s_fp[a] = mine ? saved[n + i] : 0.0;
@@ -397,7 +398,7 @@ __global__ __launch_bounds__(64 * LANES) void k_eam_adjoint_rows(
           f2 = fma(s_w[q], __builtin_nontemporal_load(jac + (size_t)(T.first + q) * g.n_rho + k),
                    f2);
         h += v;
-        hf = fma(s_fp[q], v, hf);
+        hf = v != 0.0 ? fma(s_fp[q], v, hf) : hf;
       }
     }
     s_phi[c] = 0.25 * g.r_inv_h * h;
@@ -429,7 +430,10 @@ __global__ __launch_bounds__(64 * LANES) void k_eam_adjoint_rows(
       const int k = lane + c * MD_WAVE;
       double f2 = 0.0;
       if (k < g.n_rho)
-        for (int q = wid; q < T.count; q += nw) f2 = fma(s_w[q], rows[(size_t)q * g.stride + k], f2);
+        for (int q = wid; q < T.count; q += nw) {
+          const double v = rows[(size_t)q * g.stride + k];
+          f2 = v != 0.0 ? fma(s_w[q], v, f2) : f2;
+        }
       s_rho[c] = fma(f2, 1.0 / 6.0, s_rho[c]);
     }
     __syncthreads();

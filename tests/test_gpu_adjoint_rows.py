@@ -61,6 +61,22 @@ def test_gradient_by_rows(n, jac):
             assert np.max(np.abs(g[k * n:(k + 1) * n] - want)) <= 1e-12 * scale, (lanes, k)
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_coefficients_no_pair_reads(bad):
+    """A non-finite rho coefficient below every distance: both ways leave it out."""
+    from paper_2511_22951_amd import fm
+    snaps, pot = _snapshots(), _potential(64)
+    pot.coef[1][:2] = bad
+    cot = np.random.default_rng(3).normal(size=(sum(len(s.pos) for s in snaps), 3))
+    grads = []
+    for lanes in (2, 4):
+        batch = fm.SnapshotBatch(snaps, 5.8, lanes=lanes, density_jacobian=False)
+        batch.forces(pot)
+        grads.append(batch.backward(pot, batch.to_current_order(cot)).cpu().numpy())
+    assert np.all(np.isfinite(grads[0]))
+    assert np.max(np.abs(grads[1] - grads[0])) <= 1e-12 * np.max(np.abs(grads[0]))
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("lanes", [1, 4])
 def test_lj_streamed_list(lanes, prec):
