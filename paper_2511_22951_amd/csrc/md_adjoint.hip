@@ -294,8 +294,11 @@ __global__ __launch_bounds__(64 * LANES) void k_eam_adjoint(
 // 512,000 atoms (1024 boxes), 64 coefficients, with the Jacobian: 210 us, 248 by the bins of
 // k_eam_adjoint (LDS pipe 57 % busy, texture-data path 90 %: now bound by the gathers of six
 // doubles per pair; four blocks of 35 KB per CU).  One entry in flight per lane 270 us, four 226
-// (94 registers).  At 2 lanes and 1 a block has only two wavefronts or one beside its rows: those
-// take k_eam_adjoint, as do splines of more coefficients than two such blocks per CU hold.
+// (94 registers).  At 2 lanes and 1 a block has only two wavefronts or one beside its rows (rows
+// and bins at 2 lanes: 277 and 296 us, 253,952 atoms 138 and 136, without the
+// Jacobian 376 and 321); without the Jacobian and with a CU for every block the second set of rows
+// costs more than the adds (9,472 atoms, 4 lanes: 22.4 and 21.4 us; 512,000 atoms 276 and 309).
+// Those take k_eam_adjoint, as do splines of more coefficients than two such blocks per CU hold.
 template <int LANES, int U, bool JAC>
 __global__ __launch_bounds__(64 * LANES) void k_eam_adjoint_rows(
     md_batch b, const double4* __restrict__ pos, const int* __restrict__ neigh,
@@ -637,8 +640,8 @@ int backward(const md_batch* b, const md_eam* p, md_precision prec, const double
     const int row = g.n_rho | 1;  // an odd number of doubles: equal columns on different banks
     const size_t row_lds =
         ((size_t)MD_TILE * (row + 2) + g.n_rho + (size_t)nw * g.n_emb) * sizeof(double);
-    if (L >= 4 && g.n_rho <= MD_ROWS_MAX_COEF && nw * n_hot <= MD_TILE * row &&
-        row_lds <= MD_ROWS_LDS) {
+    if (L >= 4 && (jac || b->n_tiles > 256) && g.n_rho <= MD_ROWS_MAX_COEF &&
+        nw * n_hot <= MD_TILE * row && row_lds <= MD_ROWS_LDS) {
       g.stride = row;
 #define MD_ADJ_ROWS(LN, J)                                                                     \
   MD_LAUNCH_TIMED(MD_KERNEL_EAM_ADJOINT, (k_eam_adjoint_rows<LN, MD_ADJ_U, J>), grid, block,    \

@@ -15,10 +15,12 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def _snapshots():
+def _snapshots(big=False):
+    """Three boxes (17 tiles), or one more of 250 tiles: past 256, where the adjoint without the
+    Jacobian goes by rows too."""
     rng = np.random.default_rng(21)
     out = []
-    for cells in ((4, 4, 4), (5, 5, 5), (4, 4, 5)):
+    for cells in ((4, 4, 4), (5, 5, 5), (4, 4, 5)) + (((20, 20, 10),) if big else ()):
         pos, box = mi.fcc_lattice(*cells, 3.7)
         out.append(SimpleNamespace(pos=mi.wrap_into_box(pos + rng.normal(0, 0.08, pos.shape), box),
                                    box=box))
@@ -38,7 +40,7 @@ def _potential(n):
 @pytest.mark.parametrize("n", [6, 7, 63, 64, 65, 100, 128, 129, 300])
 def test_gradient_by_rows(n, jac):
     from paper_2511_22951_amd import fm
-    snaps, pot = _snapshots(), _potential(n)
+    snaps, pot = _snapshots(not jac), _potential(n)
     rng = np.random.default_rng(n)
     cot = [rng.normal(size=s.pos.shape) for s in snaps]
     grads = {}
@@ -65,7 +67,7 @@ def test_gradient_by_rows(n, jac):
 def test_coefficients_no_pair_reads(bad):
     """A non-finite rho coefficient below every distance: both ways leave it out."""
     from paper_2511_22951_amd import fm
-    snaps, pot = _snapshots(), _potential(64)
+    snaps, pot = _snapshots(True), _potential(64)
     pot.coef[1][:2] = bad
     cot = np.random.default_rng(3).normal(size=(sum(len(s.pos) for s in snaps), 3))
     grads = []
