@@ -800,8 +800,9 @@ __global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
       }
     }
     const int key = (k[0] * 3 + k[1]) * 3 + k[2];
-    const bool joins = lane > 0 && lane < 27 && __shfl_up(start + cnt, 1, MD_WAVE) == start &&
-                       __shfl_up(key, 1, MD_WAVE) == key;
+    // (both exchanges before any test: a shuffle from a lane that && switched off reads 0)
+    const int prev_end = __shfl_up(start + cnt, 1, MD_WAVE), prev_key = __shfl_up(key, 1, MD_WAVE);
+    const bool joins = lane > 0 && lane < 27 && prev_end == start && prev_key == key;
     const unsigned long long heads = __builtin_amdgcn_ballot_w64(lane < 27 && !joins);
     if (lane < 27 && !joins) {
       const int r = lanes_below(heads);

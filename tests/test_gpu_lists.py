@@ -170,3 +170,33 @@ def test_batch_of_uneven_boxes(lanes):
         for i, w in enumerate(lists([(p, b)])):
             assert np.array_equal(got[first + i] - first, w), (first, i)
         first += len(p)
+
+
+def _gas(cells, n, seed, r_ns=5.0, edge=5.3):
+    """n atoms anywhere in a periodic box of the given cells, several boxes' worth of seeds."""
+    box = mi.Box((0.0, 0.0, 0.0), tuple(edge * c for c in cells), (1, 1, 1))
+    pos = np.random.default_rng(seed).uniform(0.0, 1.0, (n, 3)) * box.len
+    return pos, box, r_ns
+
+
+@pytest.mark.parametrize("cells,n", [((3, 3, 3), 14), ((3, 3, 3), 27), ((4, 4, 4), 32),
+                                     ((3, 4, 5), 40), ((4, 3, 3), 64)])
+def test_dilute_periodic_gases(cells, n):
+    """A few atoms on the smallest grids of the matrix form: the runs of stencil cells that
+    follow one another in memory begin and end at empty cells, at the first atom and at wraps."""
+    for seed in range(24):
+        _check(*_gas(cells, n, seed), lanes=1 + seed % 2)
+
+
+def test_first_cell_of_the_box_after_its_image():
+    """Cell (1, 1, 0) reads (0, 0, 2) through the boundary, then (0, 0, 0), which starts at atom 0
+    without an image, with (0, 1, 0) and (0, 1, 1) empty and (0, 1, 2) next in memory."""
+    e = 5.3
+    box = mi.Box((0.0, 0.0, 0.0), (3 * e, 3 * e, 3 * e), (1, 1, 1))
+    at = {(0, 0, 0): [(4.9, 4.8, 0.4), (4.5, 4.9, 0.9)], (0, 0, 2): [(4.7, 4.7, 15.5)],
+          (0, 1, 2): [(5.0, 5.6, 15.4), (5.1, 6.0, 15.0)], (1, 1, 0): [(5.5, 5.5, 0.2), (5.7, 5.4, 1.0)]}
+    pos = np.array([x for cell in at for x in at[cell]])
+    cell = np.repeat(list(at), [len(at[c]) for c in at], axis=0)
+    assert np.array_equal(np.floor(pos / e).astype(int), cell)
+    for lanes in (1, 4):
+        assert _check(pos, box, 5.0, lanes) == len(pos) - 1
