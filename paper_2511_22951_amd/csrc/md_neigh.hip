@@ -719,8 +719,10 @@ __device__ __forceinline__ void atom_lists(const md_domain& D, int a0, int na, i
 
 // One block per cell.  The fixed image of a stencil cell is the minimum image of every pair
 // that can be closer than r_ns when each periodic axis has at least three cells of edge w >
-// r_ns and every candidate lies in its cell; the second is checked while staging (|u| <= 1.5 w
-// per axis; not so if positions changed since the binning, left a wall or are not finite).
+// r_ns, the cell's own atoms lie within w / 2 of its centre and every candidate's image within
+// 1.5 w of it per axis: the other images are then 3 w - 2 w > r_ns away or farther.  Both are
+// checked while staging (not so if positions changed since the binning, left a wall or are not
+// finite).
 // Cells for which either fails, or with more candidates than LDS holds, take the FP64 form,
 // their atoms shared among the wavefronts.
 //
@@ -786,7 +788,8 @@ __global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
     double off[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const double width = __builtin_amdgcn_rcp(D.inv_w[q]);  // (to 1e-7: its uses have slack)
+      double width = __builtin_amdgcn_rcp(D.inv_w[q]);  // 1 / inv_w, refined once
+      width = fma(width, fma(-D.inv_w[q], width, 1.0), width);
       const double ctr = D.lo[q] + (cc[q] + 0.5) * width;
       off[q] = (double)k[q] * D.len[q] + ctr;
       if (lane == 0) {
@@ -849,7 +852,8 @@ __global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
       for (int q = lane; q < n; q += MD_WAVE) {
         const double4 p = pos[j0 + q];
         const double ux = p.x - ox, uy = p.y - oy, uz = p.z - oz;
-        bad |= !(fabs(ux) <= ex && fabs(uy) <= ey && fabs(uz) <= ez);
+        const double m = (unsigned)(j0 + q - a0) < (unsigned)na ? 3.0 : 1.0;  // the cell's own
+        bad |= !(m * fabs(ux) <= ex && m * fabs(uy) <= ey && m * fabs(uz) <= ez);
         const float x = (float)ux, y = (float)uy, z = (float)uz;
         const int v = v0 + q;
         *reinterpret_cast<f32x4*>(recs[v + pad * segment_of(v, S)]) =

@@ -200,3 +200,26 @@ def test_first_cell_of_the_box_after_its_image():
     assert np.array_equal(np.floor(pos / e).astype(int), cell)
     for lanes in (1, 4):
         assert _check(pos, box, 5.0, lanes) == len(pos) - 1
+
+
+@pytest.mark.parametrize("cells", [3, 4])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_own_atom_moved_out_of_its_cell(cells, axis, sign):
+    """An atom that left its cell for the far side of the next one, and one of the cell on the
+    other side: 2.2 cell edges apart, 0.8 through the boundary of a three-cell axis."""
+    w = 6.2
+    box = mi.Box((0.0, 0.0, 0.0), (cells * w,) * 3, (1, 1, 1))
+    a = np.full(3, 1.5 * w)  # the centre of cell (1, 1, 1)
+    b = a.copy()
+    b[axis] -= sign * 1.2 * w
+    pos = np.stack([a, b])
+    cell = np.floor(pos / w).astype(int) % cells
+    order = np.lexsort(cell.T[::-1])
+
+    def move(n):
+        d = np.zeros((2, 3))
+        d[0, axis] = sign * w
+        return d[order]
+
+    assert _check(pos, box, 5.8, move=move) == (1 if cells == 3 else 0)
