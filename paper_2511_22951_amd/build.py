@@ -19,9 +19,10 @@ BUILD = os.path.join(HERE, "_build")
 
 SOURCES = ["md_api.hip", "md_neigh.hip", "md_tables.hip", "md_force.hip", "md_verlet.hip",
            "md_adjoint.hip", "md_profile.hip", "md_bpnn.hip"]
-# md_bpnn.hip: its loops use more FP64 constants than registers can hold beside the accumulators;
-# hoisted out of the loops they spill (83 VGPRs in the symmetry-function kernel), kept in they do not
-EXTRA = {"md_neigh.hip": ["-ffp-contract=off"],
+# -disable-machine-licm: md_bpnn.hip's loops use more FP64 constants than registers can hold beside
+# the accumulators; hoisted out of the loops they spill (83 VGPRs in the symmetry-function kernel),
+# kept in they do not.  In md_neigh.hip the strided list build spills 3 VGPRs without it.
+EXTRA = {"md_neigh.hip": ["-ffp-contract=off", "-mllvm", "-disable-machine-licm"],
          "md_bpnn.hip": ["-mllvm", "-disable-machine-licm"]}
 ARCH = os.environ.get("MD950_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -368,6 +368,8 @@ __global__ __launch_bounds__(1024) void k_bin_small(md_batch b, int mode, double
 // ---------------------------------------------------------------------------
 constexpr int CW = 4;                  // wavefronts per block
 constexpr int CELL_BLOCK = CW * MD_WAVE;
+constexpr int STRIDE_GRID = 8192;      // most blocks of k_build_strided
+constexpr int GRID_CELLS = 1 << 23;    // most cells that get a block each
 constexpr int SEG_MAX = 64;            // most candidates per four-lane segment (16 segments)
 constexpr int LSLOT = 130;             // list slots per atom in LDS (a stride of 65 banks)
 
@@ -377,7 +379,7 @@ struct CellLds {
   int beg[33], start[32];                  // cell_lists: stencil ranges' first candidates, atoms
   // found by the first wavefront: runs of stencil cells that follow one another in memory with
   // one image (the z-neighbours where they do not wrap)
-  int n_runs, C, own, a0, na, img, fixed, rep;
+  int n_runs, C, own, a0, na, img, fixed, rep, out;
   int run_v[28], run_j[27];                // first candidate and first atom
   double run_off[27][3];                   // L k + cell centre
   double ctr[3], edge[3];                  // the cell's centre, 1.5 cell edges
@@ -388,6 +390,11 @@ struct CellLds {
 static inline size_t candidate_lds(int seg) {
   return std::max<size_t>(16 * (seg + 4) * 16 + 16 * seg * 4, CW * 3 * MD_WAVE * sizeof(double));
 }
+
+// What a build only reads, in the constant address space: uniform reads are scalar loads also
+// after stores (in the loop of k_build_strided).
+#define MD_CONST __attribute__((address_space(4)))
+using Domain = const md_domain MD_CONST;
 
 using f32x4 = float __attribute__((ext_vector_type(4)));
 
@@ -444,17 +451,21 @@ __device__ __forceinline__ bool accept_pair(const Cand& c, double (*s_p)[MD_WAVE
   return c.valid & (c.j != ia) & (r2 < rns2);
 }
 
+// v of lane `src` (all lanes on).
+__device__ __forceinline__ int from_lane(int src, int v) {
+  return __builtin_amdgcn_ds_bpermute(src << 2, v);
+}
+
 // Overflow flag and longest list of a wavefront's atoms.  The longest list is one word for all
 // wavefronts: only those that raise it touch it with an atomic (one atomicMax per wavefront, all
 // to one address, took 10 ns each one after the other and set the whole build's time: 118 us on
 // 131k Cu atoms whatever the rest of the kernel did).
-__device__ __forceinline__ void publish_counts(int over, int most, md_ctl_dev* ctl) {
-  const int lane = threadIdx.x & (MD_WAVE - 1);
+__device__ __forceinline__ void publish_counts(int lane, int over, int most, md_ctl_dev* ctl) {
   if (__any(over)) {
     if (lane == 0) md_flag(ctl, MD_FLAG_NEIGH_OVERFLOW);
   }
 #pragma unroll
-  for (int o = MD_WAVE / 2; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, MD_WAVE));
+  for (int o = MD_WAVE / 2; o > 0; o >>= 1) most = max(most, from_lane(lane ^ o, most));
   if (lane == 0 &&
       most > __hip_atomic_load(&ctl->max_nneigh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
     atomicMax(&ctl->max_nneigh, most);
@@ -462,13 +473,12 @@ __device__ __forceinline__ void publish_counts(int over, int most, md_ctl_dev* c
 
 // The lists of a cell by FP64 tests: the general form, for grids whose cells hold several
 // images of a pair (two cells on a periodic axis) and for cells that k_build cannot stage.
-__device__ __forceinline__ void cell_lists(const md_domain& D, int a0, int na, int C,
+__device__ __forceinline__ void cell_lists(int lane, Domain& D, int a0, int na, int C,
                                            const int* s_beg, const int* s_start,
                                            double (*s_p)[MD_WAVE],
                                            const double4* __restrict__ pos, int* neigh,
                                            int* nneigh, int max_neigh, int lanes_log2, int npad,
                                            double rns2, bool img, int& over, int& most) {
-  const int lane = threadIdx.x & (MD_WAVE - 1);
   const unsigned row = (unsigned)npad << lanes_log2;  // ints per list row
   double len[3], inv[3];
   int per[3];
@@ -568,13 +578,13 @@ __device__ __forceinline__ int segment_of(int v, int S) {
 // any element is within tau of zero (about 1 % of the four-atom groups of a thermal crystal),
 // the group's accepted candidates, with tau added to r_ns^2, are tested again in FP64
 // (accept_pair's operations: d - L k with the image k of the candidate's stencil cell).
-__device__ __forceinline__ void atom_lists(const md_domain& D, int a0, int na, int t, int S, int own, CellLds& s,
+__device__ __forceinline__ void atom_lists(int lane, Domain& D, int a0, int na, int t,
+                                           int S, int own, CellLds& s,
                                            const float (*recs)[4], const int* cand, int w,
                                            const double4* __restrict__ pos, int* neigh,
                                            int* nneigh, int max_neigh, int lanes_log2,
                                            unsigned row, double rns2, bool img, int& over,
                                            int& most) {
-  const int lane = threadIdx.x & (MD_WAVE - 1);
   const int col = lane & 3, seg = lane >> 2;
   const int pad = (S & 4) ? 0 : 4;  // rows of 4 mod 8 records: the LDS reads meet no bank twice
   const int S1 = S + pad;
@@ -667,8 +677,8 @@ __device__ __forceinline__ void atom_lists(const md_domain& D, int a0, int na, i
   int incl = mine;
   incl += row_shr<4>(incl);
   incl += row_shr<8>(incl);
-  const int r0 = __shfl(incl, 12 + col, MD_WAVE), r1 = __shfl(incl, 28 + col, MD_WAVE);
-  const int r2 = __shfl(incl, 44 + col, MD_WAVE), r3 = __shfl(incl, 60 + col, MD_WAVE);
+  const int r0 = from_lane(12 + col, incl), r1 = from_lane(28 + col, incl);
+  const int r2 = from_lane(44 + col, incl), r3 = from_lane(60 + col, incl);
   incl += (lane >= 16 ? r0 : 0) + (lane >= 32 ? r1 : 0) + (lane >= 48 ? r2 : 0);
   const int tot = r0 + r1 + r2 + r3;
   // the two parts side by side, an entry of each per trip
@@ -708,7 +718,7 @@ __device__ __forceinline__ void atom_lists(const md_domain& D, int a0, int na, i
   // rows: the four atoms' entries of a row are contiguous; a lane keeps its place in the row
   // (W = 4 lanes ints, a divisor of 64) and steps over rows
   const int W = 4 << lanes_log2, c = lane & (W - 1), i = c >> lanes_log2;
-  const int last = __shfl(min(ia < na ? tot : 0, lim), i, MD_WAVE);
+  const int last = from_lane(i, min(ia < na ? tot : 0, lim));
   int q = lane / W, at = (q << lanes_log2) + (c & ((1 << lanes_log2) - 1));
   const int step = MD_WAVE / W;
   int* to = neigh + ((size_t)(a0 + t) << lanes_log2) + (size_t)q * row + c;
@@ -717,7 +727,7 @@ __device__ __forceinline__ void atom_lists(const md_domain& D, int a0, int na, i
   wave_sync();
 }
 
-// One block per cell.  The fixed image of a stencil cell is the minimum image of every pair
+// The lists of one cell, by a block.  The fixed image of a stencil cell is the minimum image of every pair
 // that can be closer than r_ns when each periodic axis has at least three cells of edge w >
 // r_ns, the cell's own atoms lie within w / 2 of its centre and every candidate's image within
 // 1.5 w of it per axis: the other images are then 3 w - 2 w > r_ns away or farther.  Both are
@@ -726,40 +736,36 @@ __device__ __forceinline__ void atom_lists(const md_domain& D, int a0, int na, i
 // Cells for which either fails, or with more candidates than LDS holds, take the FP64 form,
 // their atoms shared among the wavefronts.
 //
-// Bound by latency: of 69 us for 131k Cu atoms (78 of 515 candidates accepted per atom, 41
+// Bound by latency: of 66 us for 131k Cu atoms (78 of 515 candidates accepted per atom, 41
 // MB of lists, an 8 us write) the vector units are busy for 46; finding the runs takes about 20,
 // the staging 10, the tests 20 and the entries the rest, much of it overlapped by the eight
-// blocks of a CU.  Before: one wavefront per cell testing 64 candidates against one atom at a
-// time in FP64, 118 us (98 us without its same-address atomics, see publish_counts); 864,000
-// argon atoms 361 us, 541 before.  Entries stored one by one as they are found (scattered words,
+// blocks of a CU (59 VGPRs; 20 KB of LDS each at 640 candidates).  Before: one wavefront per cell
+// testing 64 candidates against one atom at a time in FP64, 118-126 us (98 us without its
+// same-address atomics, see publish_counts); 864,000 argon atoms 305 us, 551 before.  Measured at
+// 69 us for the Cu build: entries stored one by one as they are found (scattered words,
 // 11 per instruction) took 44 us of such a build, and 16 atoms per matrix instruction (two
 // groups for the 19 atoms of a cell, the second nearly empty) left the lanes a fifth full while
-// listing: 114 us.  Three wavefronts per block 76 us, two 78, five 88.
-__global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
-                                                         const double4* __restrict__ pos,
-                                                         const int* __restrict__ cell_start,
-                                                         int* neigh, int* nneigh, int max_neigh,
-                                                         int lanes_log2, int npad, double rns2,
-                                                         int seg, md_ctl_dev* ctl) {
-  if (skip_rebuild(mode, ctl)) return;
-  extern __shared__ double s_dyn[];
-  __shared__ CellLds s;
+// listing: 114 us; three wavefronts per block 76 us, two 78, five 88.
+__device__ __forceinline__ void build_cell(Domain* domains, int n_rep, int cell, int tid,
+                                           CellLds& s, double* s_dyn,
+                                           const double4* __restrict__ pos,
+                                           const int* __restrict__ cell_start, int* neigh,
+                                           int* nneigh, int max_neigh, int lanes_log2, int npad,
+                                           double rns2, int seg, md_ctl_dev* ctl) {
   float(*recs)[4] = reinterpret_cast<float(*)[4]>(s_dyn);
   int* cand = reinterpret_cast<int*>(recs + 16 * (seg + 4));
-  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / MD_WAVE);
-  const int lane = threadIdx.x & (MD_WAVE - 1);
-  const int cell = md_remap_block(b.n_cells);
-  if (cell >= b.n_cells) return;
+  const int w = __builtin_amdgcn_readfirstlane(tid / MD_WAVE);
+  const int lane = tid & (MD_WAVE - 1);
   if (w == 0) {
-    const int a0 = __builtin_amdgcn_readfirstlane(cell_start[cell]);
-    const int na = __builtin_amdgcn_readfirstlane(cell_start[cell + 1]) - a0;
+    const int MD_CONST* range = (const int MD_CONST*)cell_start + cell;
+    const int a0 = range[0], na = range[1] - a0;
     // the box of this cell: the last domain whose cells start at or before it
-    int lo = 0, hi = b.n_rep - 1;
+    int lo = 0, hi = n_rep - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
-      if (b.domains[mid].cell_off <= cell) lo = mid; else hi = mid - 1;
+      if (domains[mid].cell_off <= cell) lo = mid; else hi = mid - 1;
     }
-    const md_domain& D = b.domains[lo];
+    Domain& D = domains[lo];
     const int local = cell - D.cell_off;
     const int cc[3] = {local / (D.nc[2] * D.nc[1]), (local / D.nc[2]) % D.nc[1], local % D.nc[2]};
     // lane t < 27 takes stencil cell (t / 9, t / 3 % 3, t % 3): its atom range and image
@@ -778,7 +784,7 @@ __global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
     int incl = cnt;
 #pragma unroll
     for (int o = 1; o < 32; o <<= 1) {
-      const int u = __shfl_up(incl, o, MD_WAVE);
+      const int u = from_lane(lane - o, incl);
       if (lane >= o) incl += u;
     }
     const int C = __builtin_amdgcn_readlane(incl, 31);
@@ -804,7 +810,7 @@ __global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
     }
     const int key = (k[0] * 3 + k[1]) * 3 + k[2];
     // (both exchanges before any test: a shuffle from a lane that && switched off reads 0)
-    const int prev_end = __shfl_up(start + cnt, 1, MD_WAVE), prev_key = __shfl_up(key, 1, MD_WAVE);
+    const int prev_end = from_lane(lane - 1, start + cnt), prev_key = from_lane(lane - 1, key);
     const bool joins = lane > 0 && lane < 27 && prev_end == start && prev_key == key;
     const unsigned long long heads = __builtin_amdgcn_ballot_w64(lane < 27 && !joins);
     if (lane < 27 && !joins) {
@@ -828,6 +834,7 @@ __global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
       s.na = na;
       s.img = img;
       s.fixed = fixed;
+      s.out = 0;  // a candidate outside its place
       s.rep = lo;
     }
   }
@@ -836,7 +843,7 @@ __global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
   const int na = uniform(s.na);
   if (na == 0) return;
   const int a0 = uniform(s.a0), C = uniform(s.C);
-  const md_domain& D = b.domains[uniform(s.rep)];
+  Domain& D = domains[uniform(s.rep)];
   const bool img = uniform(s.img) != 0;
   bool fixed = uniform(s.fixed) != 0;
   int over = 0, most = 0;
@@ -861,23 +868,78 @@ __global__ __launch_bounds__(CELL_BLOCK, 7) void k_build(md_batch b, int mode,
         cand[v] = j0 + q;
       }
     }
-    for (int v = C + threadIdx.x; v < 16 * S; v += CELL_BLOCK)  // past the last: far away
+    for (int v = C + tid; v < 16 * S; v += CELL_BLOCK)  // past the last: far away
       *reinterpret_cast<f32x4*>(recs[v + pad * segment_of(v, S)]) =
           f32x4{0.0f, 0.0f, 0.0f, 1e30f};
-    fixed = !__syncthreads_or(bad);
+    if (__any(bad) && lane == 0) s.out = 1;
+    __syncthreads();
+    fixed = s.out == 0;
   }
   if (fixed) {
     const int own = uniform(s.own);
     for (int t = 4 * w; t < na; t += 4 * CW)
-      atom_lists(D, a0, na, t, S, own, s, recs, cand, w, pos, neigh, nneigh, max_neigh, lanes_log2,
-                 (unsigned)npad << lanes_log2, rns2, img, over, most);
+      atom_lists(lane, D, a0, na, t, S, own, s, recs, cand, w, pos, neigh, nneigh, max_neigh,
+                 lanes_log2, (unsigned)npad << lanes_log2, rns2, img, over, most);
   } else {
     const int per = (na + CW - 1) / CW, first = min(na, w * per), n = min(na, first + per) - first;
     if (n > 0)
-      cell_lists(D, a0 + first, n, C, s.beg, s.start, (double(*)[MD_WAVE])s_dyn + 3 * w, pos, neigh, nneigh, max_neigh,
-                 lanes_log2, npad, rns2, img, over, most);
+      cell_lists(lane, D, a0 + first, n, C, s.beg, s.start, (double(*)[MD_WAVE])s_dyn + 3 * w, pos,
+                 neigh, nneigh, max_neigh, lanes_log2, npad, rns2, img, over, most);
   }
-  publish_counts(over, most, ctl);
+  publish_counts(lane, over, most, ctl);
+}
+
+struct BuildArgs {
+  md_batch b;
+  int mode, max_neigh, lanes_log2, npad, seg, chunk, n_chunks;
+  const double4* pos;
+  const int* cell_start;
+  int *neigh, *nneigh;
+  double rns2;
+  md_ctl_dev* ctl;
+};
+
+// A block per cell.
+__global__ __launch_bounds__(CELL_BLOCK, 8) void k_build(BuildArgs A) {
+  if (skip_rebuild(A.mode, A.ctl)) return;
+  extern __shared__ double s_dyn[];
+  __shared__ CellLds s;
+  const int cell = md_remap_block(A.b.n_cells);
+  if (cell >= A.b.n_cells) return;
+  build_cell((Domain*)A.b.domains, A.b.n_rep, cell, threadIdx.x, s, s_dyn, A.pos, A.cell_start,
+             A.neigh, A.nneigh, A.max_neigh, A.lanes_log2, A.npad, A.rns2, A.seg, A.ctl);
+}
+
+// The same with a limited grid: a block strides over chunks of up to 64 cells and takes the cells
+// of a chunk that hold atoms one after the other.
+//
+// The arguments are read again for each cell and the thread index is made opaque: kept across the
+// loop, addresses and lane indexes cost registers that the cell needs (18 spilled, 864,000 argon
+// atoms 493 us; now as many registers as k_build, 342 us against its 305).
+__global__ __launch_bounds__(CELL_BLOCK, 8) void k_build_strided(BuildArgs) {
+  using Args = const BuildArgs MD_CONST;
+  extern __shared__ double s_dyn[];
+  __shared__ CellLds s;
+  Args* ka = (Args*)__builtin_amdgcn_kernarg_segment_ptr();
+  if (skip_rebuild(ka->mode, ka->ctl)) return;
+  for (int k = 0;; ++k) {
+    const int at = md_remap_stride(ka->n_chunks, k), chunk = ka->chunk;
+    if (at >= ka->n_chunks) break;
+    const int first = at * chunk, last = min(first + chunk, ka->b.n_cells);
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int c = first + (tid & (MD_WAVE - 1));
+    const bool some = c < last && ka->cell_start[c + 1] > ka->cell_start[c];
+    for (unsigned long long left = __builtin_amdgcn_ballot_w64(some); left; left &= left - 1) {
+      const int cell = first + __builtin_ctzll(left);
+      Args* a = ka;
+      asm volatile("" : "+s"(a));
+      asm volatile("" : "+v"(tid));
+      build_cell((Domain*)a->b.domains, a->b.n_rep, cell, tid, s, s_dyn, a->pos, a->cell_start,
+                 a->neigh, a->nneigh, a->max_neigh, a->lanes_log2, a->npad, a->rns2, a->seg, a->ctl);
+      __syncthreads();  // the LDS is the next cell's
+    }
+  }
 }
 
 }  // namespace
@@ -951,7 +1013,6 @@ extern "C" int md_build_neighbors(const md_batch* b, md_rebuild_mode mode, const
   if (lg < 0 || nl->max_neigh < nl->lanes || nl->max_neigh % nl->lanes) return MD_ERR_ARG;
   if (!(b->r_ns > 0.0)) return MD_ERR_ARG;
   if (b->n_atoms == 0) return MD_OK;
-  const dim3 grid(md_grid_blocks(b->n_cells)), block(CELL_BLOCK);
   // LDS for 1.2 times the average number of candidates, at least 640 (eight blocks then share a
   // CU) and at most 1024; cells with more take the FP64 form.  1.6 times in a batch of several
   // boxes, whose cells differ more: 64 cubes of 4^3 to 12^3 cells (182,276 atoms, 365 to 1690
@@ -959,10 +1020,28 @@ extern "C" int md_build_neighbors(const md_batch* b, md_rebuild_mode mode, const
   const double avg = 27.0 * b->n_atoms / b->n_cells;
   const double room = b->n_rep > 1 ? 1.6 : 1.2;
   const int seg = std::min(SEG_MAX, std::max(40, (int)(room * avg / 16.0 + 4.0) / 4 * 4));
-  MD_LAUNCH_TIMED(MD_KERNEL_BUILD, k_build, grid, block, candidate_lds(seg), (hipStream_t)stream,
-                  *b, (int)mode, (const double4*)pos, cell_start, nl->neigh, nl->nneigh,
-                  nl->max_neigh, lg, md_npad(b->n_atoms), b->r_ns * b->r_ns, seg,
-                  (md_ctl_dev*)ctl);
+  BuildArgs A{*b, (int)mode, nl->max_neigh, lg, md_npad(b->n_atoms), seg, 1, 0, (const double4*)pos,
+              cell_start, nl->neigh, nl->nneigh, b->r_ns * b->r_ns, (md_ctl_dev*)ctl};
+  const dim3 block(CELL_BLOCK);
+  const hipStream_t st = (hipStream_t)stream;
+  // A block per cell, or 8192 blocks that take the cells in turn.  Rebuilds that may find nothing
+  // to do: a block per cell costs 9.6 us then for 36,000 cells and 24.6 for 107,000, the strided
+  // form 3.6 and 3.7 (and 263 against 236 us where 640,000 Al atoms are rebuilt: half a round of
+  // blocks is left over).  Grids of fewer atoms than cells: 125,000 cells with 0.5, 1 and 2 atoms
+  // each take 216, 267 and 317 us by a block per cell and 167, 256 and 340 by the strided form,
+  // 8.4 million cells with 100,000 atoms 8600 and 311 us.  And a launch holds less than 2^32
+  // threads: 2^24 blocks.
+  if (b->n_cells > STRIDE_GRID &&
+      (mode == MD_IF_FLAGGED || b->n_atoms < b->n_cells || b->n_cells > GRID_CELLS)) {
+    A.chunk = std::min(MD_WAVE, (b->n_cells + STRIDE_GRID - 1) / STRIDE_GRID);
+    A.n_chunks = (b->n_cells + A.chunk - 1) / A.chunk;
+    MD_LAUNCH_TIMED(MD_KERNEL_BUILD, k_build_strided,
+                    dim3(std::min(STRIDE_GRID, md_grid_blocks(A.n_chunks))), block,
+                    candidate_lds(seg), st, A);
+  } else {
+    MD_LAUNCH_TIMED(MD_KERNEL_BUILD, k_build, dim3(md_grid_blocks(b->n_cells)), block,
+                    candidate_lds(seg), st, A);
+  }
   MD_LAUNCH_CHECK();
   return MD_OK;
 }

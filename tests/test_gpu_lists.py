@@ -223,3 +223,69 @@ def test_own_atom_moved_out_of_its_cell(cells, axis, sign):
         return d[order]
 
     assert _check(pos, box, 5.8, move=move) == (1 if cells == 3 else 0)
+
+
+# Grids of more than 8192 cells go by blocks that take several cells in turn where atoms are fewer
+# than cells or the rebuild is conditional: beside that size, with chunks of 2 and of 64 cells, past
+# 64 x 8192 cells (blocks stride), with two cells on an axis and walls (the FP64 form in the loop)
+@pytest.mark.parametrize("cells,n,periodic", [
+    ((16, 16, 32), 3000, (1, 1, 1)), ((16, 19, 27), 3000, (1, 1, 1)), ((16, 19, 27), 8207, (1, 0, 1)),
+    ((16, 19, 27), 8208, (1, 1, 1)), ((2, 3, 1021), 4000, (1, 1, 1)), ((2, 5, 900), 6000, (1, 0, 0)),
+    ((70, 85, 90), 2000, (1, 1, 1))])
+def test_large_sparse_grids(cells, n, periodic):
+    pos, box, r_ns = _gas(cells, n, seed=n)
+    _check(pos, mi.Box(box.lo, box.len, periodic), r_ns, lanes=2)
+
+
+def test_more_cells_than_blocks_of_one_launch():
+    """17.6 million cells (a block each would be 2^32 threads and more): pairs found by brute force."""
+    from paper_2511_22951_amd import _native as N
+    from paper_2511_22951_amd import md
+    pos, box, r_ns = _gas((260, 260, 260), 300, seed=1)
+    pos[150:] = pos[:150] + np.random.default_rng(2).normal(0.0, 2.0, (150, 3))
+    pos[:3] = ((0.1, 0.2, 0.3), (1377.9, 0.3, 0.2), (1377.8, 1377.5, 1377.9))  # the corners
+    pos = mi.wrap_into_box(pos, box)
+    plan = md.Plan([box], [len(pos)], r_ns)
+    assert plan.n_cells > 1 << 24
+    st = md.State(plan, pos, None, N.MD_FP64)
+    nl = md.NeighborList(plan.n_atoms, 64, 2)
+    md.md_bin_cells(st)
+    md.md_build_neighbors(st, nl)
+    st.check_flags()
+    p, ln = st.pos[:, :3].cpu().numpy(), np.asarray(box.len)
+    d = p[None] - p[:, None]
+    d -= ln * np.rint(d / ln)
+    near = (d * d).sum(-1) < r_ns * r_ns
+    np.fill_diagonal(near, False)
+    assert near.sum() > 200
+    for i, got in enumerate(nl.host_lists()):
+        assert np.array_equal(np.sort(got), np.flatnonzero(near[i])), i
+
+
+@pytest.mark.parametrize("shape", [(18, 18, 18), (4, 40, 60)])
+def test_conditional_rebuild_of_a_large_grid(shape):
+    """9261 and 12,696 cells, two and three atoms each: nothing is written before a drift exceeds
+    half the skin, and the lists of the moved positions after."""
+    from paper_2511_22951_amd import _native as N
+    from paper_2511_22951_amd import md
+    import torch
+    pos, box = _crystal(shape, 3.615, 0.1)
+    plan = md.Plan([box], [len(pos)], 3.0)
+    assert plan.n_cells > 8192 and plan.n_atoms > plan.n_cells
+    vel = np.random.default_rng(3).normal(0.0, 1.0, pos.shape)
+    st = md.State(plan, pos, vel, N.MD_FP64)
+    nl = md.NeighborList(plan.n_atoms, 32, 2)
+    md.md_bin_cells(st)
+    md.md_build_neighbors(st, nl)
+    st.check_flags()
+    nl.neigh.fill_(-1)
+    for half_skin, moves in ((1.0, False), (1e-6, True)):
+        md.md_verlet_step(st, N.MD_KICK_DRIFT, 1e-2, 1.0 / 40.0, half_skin=half_skin)
+        md.md_bin_cells(st, N.MD_IF_FLAGGED)
+        md.md_build_neighbors(st, nl, N.MD_IF_FLAGGED)
+        assert bool((nl.neigh == -1).all()) != moves
+    assert st.check_flags()["n_rebuilds"] == 2
+    p = st.pos[:, :3].cpu().numpy()
+    want = _model(p, st.cell_start.cpu().numpy(), box, plan.cells_per_axis[0], 3.0)
+    for i, (g, w) in enumerate(zip(nl.host_lists(), want)):
+        assert np.array_equal(g, w), i
