@@ -5,6 +5,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "md_internal.h"
 
@@ -376,7 +377,8 @@ constexpr int LSLOT = 130;             // list slots per atom in LDS (a stride o
 // LDS of a block besides the candidates.
 struct CellLds {
   unsigned short list[CW][4 * LSLOT];      // the lists of a wavefront's four atoms, as candidates
-  int beg[33], start[32];                  // cell_lists: stencil ranges' first candidates, atoms
+  int beg[33];                             // cell_lists: stencil ranges' first candidates,
+  unsigned start[32];                      // atoms and images
   // found by the first wavefront: runs of stencil cells that follow one another in memory with
   // one image (the z-neighbours where they do not wrap)
   int n_runs, C, own, a0, na, img, fixed, rep, out;
@@ -427,8 +429,17 @@ __device__ __forceinline__ int stencil_cell(int c, int t, int nc, int periodic, 
 struct Cand {
   double x, y, z;     // candidate position
   int j;              // candidate index
+  unsigned image;     // of its stencil cell (image_code)
   bool valid;
 };
+
+// The images k of a stencil cell along the axes as a number below 27.  A range's first atom
+// (below 2^27) and its image share a word: LDS beyond 20 KB would cost a block its place on the CU.
+__device__ __forceinline__ unsigned image_code(const int (&k)[3]) {
+  return (unsigned)((k[0] + 1) * 9 + (k[1] + 1) * 3 + k[2] + 1);
+}
+constexpr int IMAGE_BIT = 27;
+static_assert(MD_MAX_ATOMS < 1 << IMAGE_BIT, "a range's first atom and its image share a word");
 
 // Entry `slot` of atom ia: row slot / lanes, column ia * lanes + slot % lanes.
 __device__ __forceinline__ int* entry(int* neigh, int ia, int slot, int lanes_log2,
@@ -438,15 +449,23 @@ __device__ __forceinline__ int* entry(int* neigh, int ia, int slot, int lanes_lo
          ((unsigned)slot & (lanes - 1));
 }
 
-// Candidate c against atom k of the cell (position in s_p, index ia), with the minimum
-// image per candidate.
-__device__ __forceinline__ bool accept_pair(const Cand& c, double (*s_p)[MD_WAVE], int k, int ia,
+// Candidate c against atom k of the cell (position in s_p, index ia): with FIXED by its stencil
+// cell's image (shift = L k), else with the minimum image per candidate.
+template <bool FIXED>
+__device__ __forceinline__ bool accept_pair(const Cand& c, const double (&shift)[3],
+                                            double (*s_p)[MD_WAVE], int k, int ia,
                                             const double* len, const double* inv, const int* per,
                                             double rns2) {
   double dx = c.x - s_p[0][k], dy = c.y - s_p[1][k], dz = c.z - s_p[2][k];
-  if (per[0]) dx = dx - len[0] * rint(dx * inv[0]);
-  if (per[1]) dy = dy - len[1] * rint(dy * inv[1]);
-  if (per[2]) dz = dz - len[2] * rint(dz * inv[2]);
+  if (FIXED) {
+    dx = dx - shift[0];
+    dy = dy - shift[1];
+    dz = dz - shift[2];
+  } else {
+    if (per[0]) dx = dx - len[0] * rint(dx * inv[0]);
+    if (per[1]) dy = dy - len[1] * rint(dy * inv[1]);
+    if (per[2]) dz = dz - len[2] * rint(dz * inv[2]);
+  }
   const double r2 = (dx * dx + dy * dy) + dz * dz;
   return c.valid & (c.j != ia) & (r2 < rns2);
 }
@@ -471,10 +490,15 @@ __device__ __forceinline__ void publish_counts(int lane, int over, int most, md_
     atomicMax(&ctl->max_nneigh, most);
 }
 
-// The lists of a cell by FP64 tests: the general form, for grids whose cells hold several
-// images of a pair (two cells on a periodic axis) and for cells that k_build cannot stage.
+// The lists of a cell by FP64 tests: for cells with more candidates than a block stages (FIXED),
+// and for grids whose cells hold several images of a pair (two cells on a periodic axis) and cells
+// with positions outside their places, which take the minimum image of each candidate.  Bound by
+// FP64 issue: by the stencil's images 131,072 Cu atoms at 7.8 A (1290 candidates) 217 us, at 9 A
+// (2048) 306-332, by a rounding per candidate and axis 281 and 410; one wavefront per cell that
+// loads its candidates once, with a same-address atomic, 251 and 490.
+template <bool FIXED>
 __device__ __forceinline__ void cell_lists(int lane, Domain& D, int a0, int na, int C,
-                                           const int* s_beg, const int* s_start,
+                                           const int* s_beg, const unsigned* s_start,
                                            double (*s_p)[MD_WAVE],
                                            const double4* __restrict__ pos, int* neigh,
                                            int* nneigh, int max_neigh, int lanes_log2, int npad,
@@ -496,11 +520,13 @@ __device__ __forceinline__ void cell_lists(int lane, Domain& D, int a0, int na, 
 #pragma unroll
     for (int st = 16; st > 0; st >>= 1)
       if (s_beg[r + st] <= v) r += st;
-    c.j = c.valid ? s_start[r] + (v - s_beg[r]) : a0;
+    const unsigned range = s_start[r];
+    c.j = c.valid ? (int)(range & ((1u << IMAGE_BIT) - 1)) + (v - s_beg[r]) : a0;
     const double4 q = pos[c.j];
     c.x = q.x;
     c.y = q.y;
     c.z = q.z;
+    c.image = FIXED ? range >> IMAGE_BIT : 0u;
     return c;
   };
   for (int g0 = 0; g0 < na; g0 += MD_WAVE) {
@@ -517,11 +543,18 @@ __device__ __forceinline__ void cell_lists(int lane, Domain& D, int a0, int na, 
     for (int v0 = 0; v0 < C; v0 += MD_WAVE) {
       const Cand c = nx;
       if (v0 + MD_WAVE < C) nx = make(v0 + MD_WAVE + lane);  // next chunk in flight
+      double sh[3] = {0.0, 0.0, 0.0};
+      if (FIXED) {
+        const int kx = c.image / 9, ky = c.image / 3 % 3, kz = c.image % 3;
+        sh[0] = (double)(kx - 1) * len[0];
+        sh[1] = (double)(ky - 1) * len[1];
+        sh[2] = (double)(kz - 1) * len[2];
+      }
       // two atoms per trip: their distance chains overlap
       for (int k = 0; k < gc; k += 2) {
         const int k1 = min(k + 1, gc - 1);  // gc odd: the last trip tests atom k twice
-        const bool ok0 = accept_pair(c, s_p, k, a0 + g0 + k, len, inv, per, rns2);
-        const bool ok1 = accept_pair(c, s_p, k1, a0 + g0 + k1, len, inv, per, rns2) &&
+        const bool ok0 = accept_pair<FIXED>(c, sh, s_p, k, a0 + g0 + k, len, inv, per, rns2);
+        const bool ok1 = accept_pair<FIXED>(c, sh, s_p, k1, a0 + g0 + k1, len, inv, per, rns2) &&
                          k1 != k;
         const unsigned long long m0 = __builtin_amdgcn_ballot_w64(ok0);
         const unsigned long long m1 = __builtin_amdgcn_ballot_w64(ok1);
@@ -734,7 +767,7 @@ __device__ __forceinline__ void atom_lists(int lane, Domain& D, int a0, int na, 
 // checked while staging (not so if positions changed since the binning, left a wall or are not
 // finite).
 // Cells for which either fails, or with more candidates than LDS holds, take the FP64 form,
-// their atoms shared among the wavefronts.
+// their atoms shared among the wavefronts; by the fixed images too where only the LDS lacks.
 //
 // Bound by latency: of 66 us for 131k Cu atoms (78 of 515 candidates accepted per atom, 41
 // MB of lists, an 8 us write) the vector units are busy for 46; finding the runs takes about 20,
@@ -790,7 +823,7 @@ __device__ __forceinline__ void build_cell(Domain* domains, int n_rep, int cell,
     const int C = __builtin_amdgcn_readlane(incl, 31);
     const int beg = incl - cnt;
     // the block wraps (image flag for the force passes)
-    bool img = false, fixed = C <= 16 * seg;
+    bool img = false, fixed = true;
     double off[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -808,7 +841,7 @@ __device__ __forceinline__ void build_cell(Domain* domains, int n_rep, int cell,
         fixed &= D.nc[q] >= 3 && width * width > rns2 * (1.0 + 1e-4);
       }
     }
-    const int key = (k[0] * 3 + k[1]) * 3 + k[2];
+    const int key = (int)image_code(k);
     // (both exchanges before any test: a shuffle from a lane that && switched off reads 0)
     const int prev_end = from_lane(lane - 1, start + cnt), prev_key = from_lane(lane - 1, key);
     const bool joins = lane > 0 && lane < 27 && prev_end == start && prev_key == key;
@@ -822,7 +855,7 @@ __device__ __forceinline__ void build_cell(Domain* domains, int n_rep, int cell,
     }
     if (lane < 32) {
       s.beg[lane] = lane < 27 ? beg : C;
-      s.start[lane] = start;
+      s.start[lane] = (unsigned)start | image_code(k) << IMAGE_BIT;
     }
     if (lane == 13) s.own = beg;
     if (lane == 0) {
@@ -847,44 +880,60 @@ __device__ __forceinline__ void build_cell(Domain* domains, int n_rep, int cell,
   const bool img = uniform(s.img) != 0;
   bool fixed = uniform(s.fixed) != 0;
   int over = 0, most = 0;
+  const bool staged = fixed && C <= 16 * seg;
   const int S = (C + 63) / 64 * 4;  // candidates per segment
   if (fixed) {
     const int pad = (S & 4) ? 0 : 4, n_runs = uniform(s.n_runs);
     const double ex = s.edge[0], ey = s.edge[1], ez = s.edge[2];
     bool bad = false;
-    for (int r = w; r < n_runs; r += CW) {
-      const int v0 = uniform(s.run_v[r]), n = uniform(s.run_v[r + 1]) - v0;
-      const int j0 = uniform(s.run_j[r]);
-      const double ox = s.run_off[r][0], oy = s.run_off[r][1], oz = s.run_off[r][2];
-      for (int q = lane; q < n; q += MD_WAVE) {
-        const double4 p = pos[j0 + q];
-        const double ux = p.x - ox, uy = p.y - oy, uz = p.z - oz;
-        const double m = (unsigned)(j0 + q - a0) < (unsigned)na ? 3.0 : 1.0;  // the cell's own
-        bad |= !(m * fabs(ux) <= ex && m * fabs(uy) <= ey && m * fabs(uz) <= ez);
-        const float x = (float)ux, y = (float)uy, z = (float)uz;
-        const int v = v0 + q;
-        *reinterpret_cast<f32x4*>(recs[v + pad * segment_of(v, S)]) =
-            f32x4{-2.0f * x, -2.0f * y, -2.0f * z, x * x + y * y + z * z};
-        cand[v] = j0 + q;
+    auto visit = [&](auto store) {
+      for (int r = w; r < n_runs; r += CW) {
+        const int v0 = uniform(s.run_v[r]), n = uniform(s.run_v[r + 1]) - v0;
+        const int j0 = uniform(s.run_j[r]);
+        const double ox = s.run_off[r][0], oy = s.run_off[r][1], oz = s.run_off[r][2];
+        for (int q = lane; q < n; q += MD_WAVE) {
+          const double4 p = pos[j0 + q];
+          const double ux = p.x - ox, uy = p.y - oy, uz = p.z - oz;
+          const double m = (unsigned)(j0 + q - a0) < (unsigned)na ? 3.0 : 1.0;  // the cell's own
+          bad |= !(m * fabs(ux) <= ex && m * fabs(uy) <= ey && m * fabs(uz) <= ez);
+          if constexpr (decltype(store)::value) {
+            const float x = (float)ux, y = (float)uy, z = (float)uz;
+            const int v = v0 + q;
+            *reinterpret_cast<f32x4*>(recs[v + pad * segment_of(v, S)]) =
+                f32x4{-2.0f * x, -2.0f * y, -2.0f * z, x * x + y * y + z * z};
+            cand[v] = j0 + q;
+          }
+        }
       }
+    };
+    if (staged) {
+      visit(std::true_type{});
+      for (int v = C + tid; v < 16 * S; v += CELL_BLOCK)  // past the last: far away
+        *reinterpret_cast<f32x4*>(recs[v + pad * segment_of(v, S)]) =
+            f32x4{0.0f, 0.0f, 0.0f, 1e30f};
+    } else {
+      visit(std::false_type{});
     }
-    for (int v = C + tid; v < 16 * S; v += CELL_BLOCK)  // past the last: far away
-      *reinterpret_cast<f32x4*>(recs[v + pad * segment_of(v, S)]) =
-          f32x4{0.0f, 0.0f, 0.0f, 1e30f};
     if (__any(bad) && lane == 0) s.out = 1;
     __syncthreads();
     fixed = s.out == 0;
   }
-  if (fixed) {
+  if (fixed && staged) {
     const int own = uniform(s.own);
     for (int t = 4 * w; t < na; t += 4 * CW)
       atom_lists(lane, D, a0, na, t, S, own, s, recs, cand, w, pos, neigh, nneigh, max_neigh,
                  lanes_log2, (unsigned)npad << lanes_log2, rns2, img, over, most);
   } else {
     const int per = (na + CW - 1) / CW, first = min(na, w * per), n = min(na, first + per) - first;
-    if (n > 0)
-      cell_lists(lane, D, a0 + first, n, C, s.beg, s.start, (double(*)[MD_WAVE])s_dyn + 3 * w, pos,
-                 neigh, nneigh, max_neigh, lanes_log2, npad, rns2, img, over, most);
+    auto lists = [&](auto fixed_tag) {
+      cell_lists<decltype(fixed_tag)::value>(lane, D, a0 + first, n, C, s.beg, s.start,
+                                             (double(*)[MD_WAVE])s_dyn + 3 * w, pos, neigh, nneigh,
+                                             max_neigh, lanes_log2, npad, rns2, img, over, most);
+    };
+    if (n > 0) {
+      if (fixed) lists(std::true_type{});
+      else lists(std::false_type{});
+    }
   }
   publish_counts(lane, over, most, ctl);
 }
@@ -1015,8 +1064,10 @@ extern "C" int md_build_neighbors(const md_batch* b, md_rebuild_mode mode, const
   if (b->n_atoms == 0) return MD_OK;
   // LDS for 1.2 times the average number of candidates, at least 640 (eight blocks then share a
   // CU) and at most 1024; cells with more take the FP64 form.  1.6 times in a batch of several
-  // boxes, whose cells differ more: 64 cubes of 4^3 to 12^3 cells (182,276 atoms, 365 to 1690
-  // candidates, 542 on average) take 177 us with LDS for 704, 111 for 896 and 121 for 1024.
+  // boxes, whose cells may differ more: 64 cubes of 4^3 to 12^3 cells at several densities (182,276
+  // atoms, 365 to 1690 candidates, 542 on average) take 104 us, 141 at 1.2 times; over a wider
+  // range of densities 141 and 247.  Equal boxes pay for it with 3 to 5 % (16 of 8,788 atoms
+  // 75 and 72 us, 512 of 500 atoms 120 and 114): the host does not know the boxes.
   const double avg = 27.0 * b->n_atoms / b->n_cells;
   const double room = b->n_rep > 1 ? 1.6 : 1.2;
   const int seg = std::min(SEG_MAX, std::max(40, (int)(room * avg / 16.0 + 4.0) / 4 * 4));

@@ -289,3 +289,14 @@ def test_conditional_rebuild_of_a_large_grid(shape):
     want = _model(p, st.cell_start.cpu().numpy(), box, plan.cells_per_axis[0], 3.0)
     for i, (g, w) in enumerate(zip(nl.host_lists(), want)):
         assert np.array_equal(g, w), i
+
+
+@pytest.mark.parametrize("scale", [0.0, 0.02, 2.0])
+@pytest.mark.parametrize("periodic", [(1, 1, 1), (1, 0, 1)])
+def test_dense_cells_of_few_per_axis(scale, periodic):
+    """2250 candidates per cell on 3 x 3 x 4 cells: the FP64 form by the stencil's images, or by the
+    minimum image where positions left their cells since the binning."""
+    box = mi.Box((1.0, -2.0, 0.0), (15.6, 16.5, 21.0), periodic)
+    rng = np.random.default_rng(12)
+    pos = rng.uniform(0.0, 1.0, (3000, 3)) * box.len + box.lo
+    _check(pos, box, 5.0, lanes=2, max_neigh=512, move=lambda n: rng.normal(0.0, scale, (n, 3)))
