@@ -558,13 +558,14 @@ def _gpu_time(fn, reps):
 def _replay_graph(fn, warm=2):
     """Capture fn() once into a HIP graph (after `warm` eager calls) and return replay()."""
     import torch
+    from paper_2511_22951_amd.sim import collector_held
     for _ in range(warm):
         fn()
     torch.cuda.synchronize()
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     g = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(g, stream=s):
+    with collector_held(), torch.cuda.graph(g, stream=s):
         fn()
     torch.cuda.current_stream().wait_stream(s)
     torch.cuda.synchronize()

@@ -28,6 +28,8 @@ Rebuild policies (both in the paper):
 """
 from __future__ import annotations
 
+import contextlib
+import gc
 import math
 
 import numpy as np
@@ -35,6 +37,22 @@ import torch
 
 from . import _native as N
 from . import md
+
+
+@contextlib.contextmanager
+def collector_held():
+    """No garbage collection inside: for a graph capture.  A dead graph that a reference cycle
+    keeps (an exception's traceback is enough) waits for the device when the collector destroys
+    it; during a capture that is an error in a destructor, and the process aborts.  What is dead
+    already is collected first."""
+    gc.collect()
+    on = gc.isenabled()
+    gc.disable()
+    try:
+        yield
+    finally:
+        if on:
+            gc.enable()
 
 
 def graph_period(rebuild_every, fused):
@@ -243,7 +261,7 @@ class Simulation:
         g = torch.cuda.CUDAGraph()
         self._capturing = True
         try:
-            with torch.cuda.graph(g, stream=s):
+            with collector_held(), torch.cuda.graph(g, stream=s):
                 for _ in range(steps):
                     self.step(ev)
         finally:

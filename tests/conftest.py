@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -26,3 +27,12 @@ def pytest_collection_modifyitems(config, items):
     for it in items:
         if "gpu" in it.keywords:
             it.add_marker(skip)
+
+
+@pytest.fixture(autouse=True)
+def _dead_graphs_go_between_gpu_tests(request):
+    """A test that kept an exception leaves its objects in a reference cycle, its HIP graphs among
+    them: they are destroyed here, not by a collection during a later test's capture."""
+    if "gpu" in request.keywords:
+        gc.collect()
+    yield
