@@ -163,12 +163,13 @@ constexpr int OBS_MAX_COEF = 4096;  // 64 KiB of LDS
 constexpr int OBS_GRID = 512;       // two blocks per CU
 
 struct ObsGrid {
-  double x_lo, inv_h, h;
+  double x_lo, inv_h;
   int n;  // coefficients
 };
 
 // sqrt(x) for a normal x > 0: the hardware estimate of 1 / sqrt(x) refined twice, then the
-// product's remainder added (within an ulp).
+// product's remainder added (within an ulp).  sqrt(0) is 0 (atoms at one place: their densities
+// and energies are finite), its inverse NaN (their own virials are not).
 __device__ __forceinline__ double sqrt_nr(double x, double& inv) {
   double y = __builtin_amdgcn_rsq(x);
   const double hx = 0.5 * x;
@@ -176,7 +177,7 @@ __device__ __forceinline__ double sqrt_nr(double x, double& inv) {
   for (int it = 0; it < 2; ++it) y = fma(y, fma(-hx * y, y, 0.5), y);
   const double g = x * y;
   inv = y;
-  return fma(fma(-g, g, x), 0.5 * y, g);
+  return x > 0.0 ? fma(fma(-g, g, x), 0.5 * y, g) : 0.0;
 }
 
 // Interval and local coordinate of r (the end intervals extend past the grid), and the four
@@ -563,7 +564,7 @@ extern "C" int md_atom_observables(const md_batch* b, const md_eam* eam, const m
   const bool pow2 = L == 1 || L == 2 || L == 4 || L == 8 || L == 16;
   if (pow2 && eam->phi.ncoef == eam->rho.ncoef && eam->phi.x_lo == eam->rho.x_lo &&
       eam->phi.h == eam->rho.h && eam->rho.ncoef <= OBS_MAX_COEF) {
-    const ObsGrid G{eam->rho.x_lo, 1.0 / eam->rho.h, eam->rho.h, eam->rho.ncoef};
+    const ObsGrid G{eam->rho.x_lo, 1.0 / eam->rho.h, eam->rho.ncoef};
     const size_t lds = (size_t)G.n * sizeof(double2);
     const int nlb = (b->n_tiles * L + OBS_BLOCK / MD_WAVE - 1) / (OBS_BLOCK / MD_WAVE);
     const dim3 og(std::min(md_grid_blocks(nlb), OBS_GRID)), ob(OBS_BLOCK);

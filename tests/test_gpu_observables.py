@@ -54,3 +54,31 @@ def test_pair_below_the_table_is_flagged(K):
         st, nl = _state([s], 4)
         md.md_atom_observables(st, nl, eam=pot)
         assert bool(st.read_flags()[1]["flags"] & N.FLAG_TABLE_RANGE) == close
+
+
+@pytest.mark.parametrize("n", [2002, 4097])
+@pytest.mark.parametrize("lanes", [1, 4])
+def test_atoms_at_one_place(n, lanes):
+    """Two atoms at one place, splines that reach r = 0 (the same coefficients on both sides: no
+    fit, no extrapolation), on both sides of the limit of coefficients kept in LDS: energies,
+    densities and F' are finite and reach their neighbours' virials; only the two atoms' own
+    virials have no value."""
+    from paper_2511_22951_amd import md
+    s = mi.eam_copper(cells=4)
+    s.pos = s.pos.copy()
+    s.pos[7] = s.pos[6]
+    h, e_h = 5.5 / (n - 3), 40.0 / (n - 3)
+    x, rho = (np.arange(n) - 1) * h, (np.arange(n) - 1) * e_h
+    c = (np.exp(-x) - 0.02 * x, np.exp(-0.7 * x), 0.01 * rho * rho - 0.5 * rho)
+    st, nl = _state([s], lanes)
+    e, w, rf = md.md_atom_observables(st, nl, eam=md.EAMPotential(*c, 0.0, h, 0.0, e_h, 5.5))
+    st.check_flags()
+    o = np.argsort(st.id.cpu().numpy(), kind="stable")
+    e, w, rf = e.cpu().numpy()[o], w.cpu().numpy().T[o], rf.cpu().numpy()[:, o]
+    f = [core.SplineFunc(q, 0.0, d) for q, d in zip(c, (h, h, e_h))]
+    r = core.eam(s.pos, s.box, core.EAMPotential(*f, 5.5))
+    pair = np.isin(np.arange(len(e)), (6, 7))
+    for got, want in ((e, r["e_atom"]), (rf[0], r["rhobar"]), (rf[1], r["fp"])):
+        assert np.abs(got - want).max() < 1e-12 * np.abs(want).max()
+    assert np.isnan(w[pair]).all() and np.isnan(r["w_atom"][pair]).all()
+    assert np.abs(w - r["w_atom"])[~pair].max() < 1e-11 * np.abs(r["w_atom"][~pair]).max()
