@@ -287,8 +287,8 @@ __device__ __forceinline__ int load_idx(const int* neigh, uint32_t e) {
   return *reinterpret_cast<const int*>(reinterpret_cast<const char*>(neigh) + (e << 2));
 }
 __device__ __forceinline__ int load_idx(const int* neigh, uint64_t e) { return neigh[e]; }
-// The LJ pass reads its list once a step: where it is addressed with 64 bits (far larger than the
-// last-level cache) it is streamed past the caches, so that the records stay in them.
+// The LJ pass reads its list once a step: where that is more than the last-level cache holds it is
+// addressed with 64 bits and streamed past the caches, so that the records stay in them.
 __device__ __forceinline__ int load_once(const int* neigh, uint32_t e) { return load_idx(neigh, e); }
 __device__ __forceinline__ int load_once(const int* neigh, uint64_t e) {
   return __builtin_nontemporal_load(neigh + e);
@@ -1178,10 +1178,14 @@ void launch_lj(const md_batch& b, const md_lj& p, const double* pos, const md_nl
   const int bt = block_threads(nl, b.n_tiles), TPB = bt / (64 * LANES);
   const dim3 grid(md_grid_blocks((b.n_tiles + TPB - 1) / TPB)), block(bt);
   const int npad = md_npad(b.n_atoms);
-  // lists beyond twice the 256 MB last-level cache too, to stream them (load_once): 2,048,000
-  // atoms 349 -> 340 us (before the pass had its indices in flight).  (The EAM passes' are read twice a step and gain by the caches: 640,000
-  // atoms 143 us, streamed 164.)
-  const bool big = (size_t)nl.max_neigh * npad >= ((size_t)1 << 27);
+  // Streamed (load_once) where what a pass reads is beyond the 256 MB last-level cache, whatever room
+  // the list has: per atom a position and the entries of a sphere of r_ns in cells at least as wide.
+  // FP32 at one lane, streamed and not: 702,464 atoms 130 and 114 us, 821,516 161 and 175,
+  // 1,048,576 180 and 198 (FP64 211 and 185, 261 and 278, 285 and 304).  (Lists of 2^30 entries and
+  // more need the 64 bits, and are streamed whatever they hold.)  The EAM passes' lists are read
+  // twice a step and gain by the caches: 640,000 atoms 143 us, streamed 164.
+  const double mean = std::min((double)nl.max_neigh, 4.19 * b.n_atoms / b.n_cells);
+  const bool big = md_big_list(nl, npad) || (4.0 * mean + 32.0) * b.n_atoms >= (double)(1 << 28);
 #define MD_LJ_LAUNCH2(EVB, E_, TH_)                                                            \
   MD_LAUNCH_TIMED(MD_KERNEL_LJ, (k_lj<R, LANES, EVB, E_, TH_>), grid, block, 0, st, b,        \
                   (const double4*)pos, nl.neigh, nl.nneigh, npad, c, rc2, (R*)force, vel,      \

@@ -96,3 +96,53 @@ def test_lj_streamed_list(lanes, prec):
         st.check_flags()
         out.append(st.force.clone())
     assert torch.equal(out[0], out[1]) and float(out[0].abs().max()) > 0
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("lanes", [1, 4])
+def test_lj_list_past_32_bits(lanes, prec):
+    """2048 atoms with room for 524,288 neighbours each, 2^30 entries: addressed with 64 bits and
+    streamed, the same bits as an ordinary list's."""
+    from paper_2511_22951_amd import md
+    pos, box = mi.fcc_lattice(8, 8, 8, 5.26)
+    pos = mi.wrap_into_box(pos + np.random.default_rng(2).normal(0, 0.1, pos.shape), box)
+    plan = md.Plan([box], [len(pos)], 8.8)
+    out = []
+    for max_neigh in (128, 1 << 19):
+        st = md.State(plan, pos, None, prec)
+        nl = md.NeighborList(plan.n_atoms, max_neigh, lanes)
+        md.md_bin_cells(st)
+        md.md_build_neighbors(st, nl)
+        md.md_lj_forces(st, md.lj_params(0.0104, 3.4, 8.5), nl)
+        st.check_flags()
+        out.append(st.force.clone())
+        del nl
+    assert torch.equal(out[0], out[1]) and float(out[0].abs().max()) > 0
+
+
+def test_lj_streamed_by_what_is_read():
+    """878,080 atoms read 7e7 entries (streamed), as 7 x 14 x 7 copies of a box of 1280 atoms, which is
+    not: every copy has its forces, to the rounding of the sums (the copies' positions are rounded
+    to the larger box, FP64)."""
+    from paper_2511_22951_amd import md
+    lj = md.lj_params(0.0104, 3.4, 8.5)
+    small, box = mi.fcc_lattice(5, 8, 8, 5.26)
+    small = mi.wrap_into_box(small + np.random.default_rng(2).normal(0, 0.1, small.shape), box)
+    copies = (7, 14, 7)
+    L = np.asarray(box.len)
+    shift = np.stack(np.meshgrid(*[range(c) for c in copies], indexing="ij"), -1).reshape(-1, 3)
+    big = (small[None] + shift[:, None] * L).reshape(-1, 3)
+    out = []
+    for pos, b in ((small, box), (big, mi.Box((0.0, 0.0, 0.0), tuple(L * copies), (1, 1, 1)))):
+        plan = md.Plan([b], [len(pos)], 8.8)
+        st = md.State(plan, mi.wrap_into_box(pos, b), None, 0)
+        nl = md.NeighborList(plan.n_atoms, 128, 1)
+        md.md_bin_cells(st)
+        md.md_build_neighbors(st, nl)
+        md.md_lj_forces(st, lj, nl)
+        st.check_flags()
+        out.append(st.forces())
+    assert len(big) * (4 * 4.19 * len(big) / plan.n_cells + 32) >= 1 << 28
+    # positions up to 589 A: 2^-44 A of rounding each, times the slope of the pair force (below 1 eV / A^2
+    # at the closest pair, 3.24 A: 24 eps / s^2 (26 (s/r)^14 - 7 (s/r)^8)) and 90 pairs
+    assert np.abs(out[1].reshape(-1, len(small), 3) - out[0]).max() < 90 * 2.0 ** -43
