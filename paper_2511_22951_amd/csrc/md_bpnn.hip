@@ -443,9 +443,10 @@ __global__ __launch_bounds__(64 * WPB, FAST && NEU <= 6 ? 3 : 2) void k_bpnn_des
     for_pairs_in_cutoff(P, s, nc, [&](int j, int k, bool active) {
       const Trip t = triplet(P, s, j, k);
       const double f3 = active ? t.fAB * t.fC : 0.0;
+      const bool on = f3 != 0.0;  // (an idle lane's powers may overflow: 0 times them is not 0)
       double Pw[NZ], none[NZ];
-      pair_powers<FAST, false>(P, t.cos, Pw, none);
-      for_exp_pairs<0, NEU, FAST>(P, s_exp, exp_at<FAST>(P, t.s2),
+      pair_powers<FAST, false>(P, on ? t.cos : 0.0, Pw, none);
+      for_exp_pairs<0, NEU, FAST>(P, s_exp, exp_at<FAST>(P, on ? t.s2 : 0.0),
                                   [&](auto U, const double (&X)[2]) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -745,7 +746,8 @@ __global__ __launch_bounds__(MD_ATOM_BLOCK) void k_bpnn_kick(md_batch b, const d
 }
 
 // Whether the set can take the FAST evaluation, and its grid in that order.  The rule is what
-// the evaluation can represent: every zeta a power of two with at most NL distinct values, and
+// the evaluation can represent: every zeta a power of two with at most NL distinct values (up to
+// 512: both signs of lambda are formed, and 1024 2^1023 overflows in the one that no function has), and
 // |eta| small enough for the exponential table's Taylor factor, |eta| 3 r_c^2 / (2 NT) <= X_MAX
 // (|eta| r_c^2 <= 4.2).  Wherever it holds it is the faster one: 32,000 Cu atoms 1.37 ms against
 // 2.48 ms for the general form (48 functions with one zeta of 3 in place of 4), 864 atoms 0.100
@@ -754,7 +756,7 @@ void fast_grid(BpnnDev* d) {
   int lev[NZ], nlev = 0;  // distinct zeta, ascending
   for (int v = 0; v < d->n_zl; ++v) {
     const int z = d->izeta_v[v];
-    if (z < 1 || (z & (z - 1))) return;
+    if (z < 1 || z > 512 || (z & (z - 1))) return;
     int l = 0;
     while (l < nlev && lev[l] < z) ++l;
     if (l < nlev && lev[l] == z) continue;

@@ -116,3 +116,15 @@ def test_several_atoms_per_wavefront():
     assert np.abs(f - f1).max() <= 1e-10 * np.abs(f1).max()
     assert np.abs(e - e1).max() <= 1e-11 * np.abs(e1).max()
     assert abs(rec[0] - len(shifts) * e1.sum()) <= 1e-11 * abs(rec[0])
+
+
+@pytest.mark.parametrize("zeta", [512.0, 1024.0, 1024.5])
+@pytest.mark.parametrize("lams", [[1.0], [-1.0], [1.0, -1.0]])
+def test_powers_near_the_largest_double(zeta, lams):
+    """2^zeta at and past the range of a double, which only a pair of neighbours in one direction
+    reaches: a centred tetrahedron has none, and most lanes have no pair at all."""
+    c = np.array([[0.0, 0.0, 0.0], [1.0, 1.0, 1.0], [1.0, -1.0, -1.0], [-1.0, 1.0, -1.0],
+                  [-1.0, -1.0, 1.0]])
+    pos = 12.0 + 1.3 * c + np.random.default_rng(8).normal(0.0, 0.02, c.shape)
+    box = mi.Box((0.0, 0.0, 0.0), (24.0, 24.0, 24.0), (1, 1, 1))
+    _compare(pos, box, _params([zeta, 2.0], lams, [0.0, 0.01]))
