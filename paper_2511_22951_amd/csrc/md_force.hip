@@ -899,8 +899,12 @@ struct LJc {
   double sig2, eps4, eps24, ucut;
 };
 
+// FP32 passes have to fit 64 registers, two workgroups of 1024 threads per CU: with the next indices
+// in flight the forms of 4 and 8 lanes took 66 and 68 unbounded and half the wavefronts (256,000
+// atoms, 1024 threads: 55 and 83 us; bounded, without a spill, 43 and 58; with indices and records
+// in turn 48 and 61).
 template <typename R, int LANES, bool EV, typename E, bool THERMO>
-__global__ __launch_bounds__(FBLOCK) void k_lj(
+__global__ __launch_bounds__(FBLOCK, sizeof(R) == 4 && !THERMO ? 8 : 4) void k_lj(
     md_batch b, const double4* __restrict__ pos, const int* __restrict__ neigh,
     const int* __restrict__ nneigh, int npad, LJc c, R rc2, R* force, double* vel,
     double inv_mass, double half_dt, DriftArgs dr, const uint4* __restrict__ rec, long long* ev,
