@@ -1088,12 +1088,16 @@ int launch_eam(const md_batch& b, const md_eam& p, const char* tab, const md_tab
   const bool ld = table_in_lds<R>(rows, MD_RTAB_W);
   const size_t lds_d = ld ? (size_t)rows * MD_RTAB_W * sizeof(R) : 0;
   const size_t lds_f = ld ? (size_t)rows * MD_FTAB_W * sizeof(R) : 0;
-  // tables that take no time to stage (coarse splines): the smallest workgroups, which wait less
-  // for their slowest wavefront (512,000 atoms, FP64, 61 intervals: both passes 224-228 us with
-  // 1024 threads, 219 with 512, 220 with 256; forces from the density Jacobian 171, 167, 166).
-  // Fused drifts keep block_threads' choice, which their displacement slots are checked for.
+  // Tables that take no time to stage (coarse splines), beyond a 1024-thread block per CU: the
+  // smallest workgroups, which wait less for their slowest wavefront (512,000 atoms, FP64, 61
+  // intervals: both passes 224-228 us with 1024 threads, 219 with 512, 220 with 256; forces from the
+  // density Jacobian 171, 167, 166; 70,304 atoms at 4 lanes, 275 blocks of 1024, 64 and 49).  Up to there block_threads'
+  // choice is the better one (65,000 atoms, 254 blocks of 1024: 38 us, 42 with 256 threads).
+  // Fused drifts keep it too: their displacement slots are checked for it.
   int bt = block_threads(nl, b.n_tiles);
-  if (!nl.block && ld && lds_d <= 16384 && !dr.pos_out) bt = std::max(256, 64 * LANES);
+  if (!nl.block && ld && lds_d <= 16384 && !dr.pos_out &&
+      (size_t)b.n_tiles * LANES > (size_t)256 * (FBLOCK / 64))
+    bt = std::max(256, 64 * LANES);
   const int TPB = bt / (64 * LANES);
   const dim3 grid(md_grid_blocks((b.n_tiles + TPB - 1) / TPB)), block(bt);
 #define MD_EAM_LAUNCH(EVB, TL_, E_, TH_)                                                          \

@@ -51,3 +51,28 @@ def test_chosen_block(shape, lanes, prec):
             assert torch.equal(f, f0), block
             tol = (1e-6 if prec else 1e-12) * np.max(np.abs(e0)) + tiles * 2.0 ** -36
             assert np.all(np.abs(e - e0) <= tol), (block, e, e0)
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 64), (16, 16, 65), (4, 4, 4)])
+@pytest.mark.parametrize("lanes", [2, 4, 8])
+def test_chosen_block_coarse_table(shape, lanes):
+    """A table of 61 intervals, at most a 1024-thread workgroup per CU (1024 tiles at 4 lanes) and
+    more: forces bit for bit those of every explicit workgroup size."""
+    from paper_2511_22951_amd import md
+    pos, box = displaced(0, 3.615, 0.05, 11, shape=shape)
+    plan = md.Plan([box], [len(pos)], 5.8)
+    st = md.State(plan, pos, None, 0)
+    nl = md.NeighborList(plan.n_atoms, 128, lanes)
+    md.md_bin_cells(st)
+    md.md_build_neighbors(st, nl)
+    pot = md.EAMPotential.from_table(mi.tabulate_eam(mi.EAM_CU, K=62))
+    table = pot.table(0)
+    forces = []
+    for block in (0, 256, 512, 1024):
+        if block and block < 64 * lanes:
+            continue
+        nl.set_block(block)
+        md.md_eam_forces(st, pot, nl, table=table)
+        st.check_flags()
+        forces.append(st.force.clone())
+    assert all(torch.equal(f, forces[0]) for f in forces) and float(forces[0].abs().max()) > 0
