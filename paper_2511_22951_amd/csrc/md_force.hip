@@ -160,16 +160,18 @@ __device__ __forceinline__ Slot force_slot(int n_tiles) {
 // Stage a table of nrows rows of W values of type R into LDS (16-byte moves).  With sixteen and
 // more moves per thread (FP64 tables of 125 KB, small blocks) eight are in flight: one at a time
 // the round trips of a block added up, FP64 passes of 8,788 atoms with 256 threads 33.9 -> 29.7
-// us, of 131,072 with 1024 72.5 -> 70.5 us.  The four moves per thread of FP32 tables and full
-// blocks lose by it (131,072 atoms, 18 steps 979 -> 1003 us).
-template <typename R, int W>
+// us, of 641,520 with 1024 at 2 lanes 303 -> 300 us.  The four moves per thread of FP32 tables and
+// full blocks lose by it (131,072 atoms, 18 steps 979 -> 1003 us), and so do 8 lanes per atom and
+// more, whose many blocks have other waves to fill the time (641,520 atoms FP64 508 -> 521 us, FP32
+// 353 -> 362).
+template <typename R, int W, int LANES>
 __device__ __forceinline__ const R* stage_table(const R* g, int nrows, R* lds) {
   const int n16 = nrows * W * (int)sizeof(R) / 16;
   const float4* src = reinterpret_cast<const float4*>(g);
   float4* dst = reinterpret_cast<float4*>(lds);
   int q = threadIdx.x;
   const int step = blockDim.x;
-  if (sizeof(R) == 8 || step < 1024) {
+  if (LANES <= 4 && (sizeof(R) == 8 || step < 1024)) {
     for (; q + 7 * step < n16; q += 8 * step) {
       float4 v[8];
 #pragma unroll
@@ -416,7 +418,7 @@ __device__ __forceinline__ void eam_density_body(
     uint4* rec, long long* ev, int ev_cap, int rec_verify, md_ctl_dev* ctl) {
   extern __shared__ float4 s_dyn[];
   __shared__ double sh[MD_EV_LEN * 16];
-  const R* rtab = TLDS ? stage_table<R, MD_RTAB_W>(rtab_g, pair_rows<R>(g), (R*)s_dyn) : rtab_g;
+  const R* rtab = TLDS ? stage_table<R, MD_RTAB_W, LANES>(rtab_g, pair_rows<R>(g), (R*)s_dyn) : rtab_g;
   if (EV && blockIdx.x == 0) zero_record(b, ev, ev_cap, ctl->step_next);
   md_step_bookkeeping(ctl, rec_verify != 0);
   const Slot S = force_slot<LANES>(b.n_tiles);
@@ -708,7 +710,7 @@ __device__ __forceinline__ void eam_force_body(
   extern __shared__ float4 s_dyn[];
   __shared__ double sh[MD_EV_LEN * 16];
   __shared__ double tsum[MD_EV_LEN * 16];
-  const R* ftab = TLDS ? stage_table<R, MD_FTAB_W>(ftab_g, pair_rows<R>(g), (R*)s_dyn) : ftab_g;
+  const R* ftab = TLDS ? stage_table<R, MD_FTAB_W, LANES>(ftab_g, pair_rows<R>(g), (R*)s_dyn) : ftab_g;
   const Slot S = force_slot<LANES>(b.n_tiles);
   double acc[7] = {0, 0, 0, 0, 0, 0, 0};  // W xx yy zz xy xz yz, K
   R fx = 0, fy = 0, fz = 0;
