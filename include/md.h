@@ -136,8 +136,9 @@ typedef struct md_nlist {
   int lanes;    /* 1, 2, 4, 8 or 16 */
   int block;    /* threads per workgroup of the force passes (the atoms one workgroup takes,
                    block / lanes, are its task): 256, 512 or 1024, at least 64 * lanes
-                   (MD_ERR_ARG otherwise), or 0 (chosen by the size of the batch).  A launch-shape choice only: results
-                   do not depend on it beyond the rounding order of the per-box records. */
+                   (MD_ERR_ARG otherwise), or 0 (chosen by the size of the batch).  A
+                   launch-shape choice only: results do not depend on it beyond the
+                   rounding order of the per-box records. */
 } md_nlist;
 
 #define MD_NN_IMG (1 << 30)

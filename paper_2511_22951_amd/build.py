@@ -20,8 +20,10 @@ BUILD = os.path.join(HERE, "_build")
 SOURCES = ["md_api.hip", "md_neigh.hip", "md_tables.hip", "md_force.hip", "md_verlet.hip",
            "md_adjoint.hip", "md_profile.hip", "md_bpnn.hip"]
 # -disable-machine-licm: md_bpnn.hip's loops use more FP64 constants than registers can hold beside
-# the accumulators; hoisted out of the loops they spill (83 VGPRs in the symmetry-function kernel),
-# kept in they do not.  In md_neigh.hip the strided list build spills 3 VGPRs without it.
+# the accumulators; hoisted out of the loops they spill (98 VGPRs in the symmetry-function kernel of
+# the common sets, 32 and more in four others).  Kept in, that kernel spills 4 VGPRs (20 bytes of
+# scratch per lane, under its bound of three waves per SIMD) and no other does.  In md_neigh.hip the
+# strided list build spills 3 VGPRs without it.
 EXTRA = {"md_neigh.hip": ["-ffp-contract=off", "-mllvm", "-disable-machine-licm"],
          "md_bpnn.hip": ["-mllvm", "-disable-machine-licm"]}
 ARCH = os.environ.get("MD950_ARCH", "gfx950")

@@ -292,8 +292,9 @@ __global__ __launch_bounds__(64 * LANES) void k_eam_adjoint(
 // Without the density Jacobian the rows are then made again of beta_k(r_ij).
 //
 // 512,000 atoms (1024 boxes), 64 coefficients, with the Jacobian: 210 us, 248 by the bins of
-// k_eam_adjoint (LDS pipe 57 % busy, texture-data path 90 %: now bound by the gathers of six
-// doubles per pair; four blocks of 35 KB per CU).  One entry in flight per lane 270 us, four 226
+// k_eam_adjoint.  Now bound by the gathers of six doubles per pair as they are laid out, a 32-byte
+// position and three arrays (texture-data path 90 % busy, LDS 53, VALU 50,
+// profiles/pass_counters.txt; four blocks of 35 KB per CU).  One entry in flight per lane 270 us, four 226
 // (94 registers).  At 2 lanes and 1 a block has only two wavefronts or one beside its rows (rows
 // and bins at 2 lanes: 277 and 296 us, 253,952 atoms 138 and 136, without the
 // Jacobian 376 and 321); without the Jacobian and with a CU for every block the second set of rows

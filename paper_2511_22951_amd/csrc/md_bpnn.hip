@@ -11,7 +11,8 @@
 // accumulates their products on the grid, so the cost per pair does not grow with
 // the number of G4 functions that share them.
 //
-// Bound by FP64 VALU issue (65 % busy in both passes, LDS next): about 1400 of an atom's 3003
+// Bound by FP64 VALU issue (131,072 Cu atoms: 90 % busy in the symmetry functions and 76 % in the
+// forces, LDS 47 and 52 %, profiles/pass_counters.txt): about 1400 of an atom's 3003
 // unordered pairs (Cu, r_c 6 A) lie within the cutoff, each worth some 170 (symmetry functions)
 // or 260 (forces) FP64 instructions.  What keeps the count there: exponentials from an LDS table
 // with a short Taylor factor and powers by shared squarings (FAST below; library exp and a

@@ -911,7 +911,8 @@ __global__ __launch_bounds__(FBLOCK, sizeof(R) == 4 && !THERMO ? 8 : 4) void k_l
     const int* __restrict__ nneigh, int npad, LJc c, R rc2, R* force, double* vel,
     double inv_mass, double half_dt, DriftArgs dr, const uint4* __restrict__ rec, long long* ev,
     int ev_cap, md_ctl_dev* ctl) {
-  // The gathers set the time (texture-data path 90 % busy).  2,048,000 atoms, FP32 at one lane: 341
+  // The gathers set the time (12,967,168 atoms, FP32 at one lane: texture-data path 96 % busy, VALU
+  // 77, profiles/pass_counters.txt).  2,048,000 atoms, FP32 at one lane: 341
   // us with indices and records loaded in turn, 325 with the next indices in flight (FP64 577 and
   // 529); two entries at a time 404, one 455, six 323 (FP64 538), eight 349.
   constexpr int U = 4;
