@@ -168,8 +168,7 @@ struct ObsGrid {
 };
 
 // sqrt(x) for a normal x > 0: the hardware estimate of 1 / sqrt(x) refined twice, then the
-// product's remainder added (within an ulp).  sqrt(0) is 0 (atoms at one place: their densities
-// and energies are finite), its inverse NaN (their own virials are not).
+// product's remainder added (within an ulp).  NaN for 0.
 __device__ __forceinline__ double sqrt_nr(double x, double& inv) {
   double y = __builtin_amdgcn_rsq(x);
   const double hx = 0.5 * x;
@@ -177,7 +176,7 @@ __device__ __forceinline__ double sqrt_nr(double x, double& inv) {
   for (int it = 0; it < 2; ++it) y = fma(y, fma(-hx * y, y, 0.5), y);
   const double g = x * y;
   inv = y;
-  return x > 0.0 ? fma(fma(-g, g, x), 0.5 * y, g) : 0.0;
+  return fma(fma(-g, g, x), 0.5 * y, g);
 }
 
 // Interval and local coordinate of r (the end intervals extend past the grid), and the four
@@ -254,8 +253,10 @@ __global__ __launch_bounds__(OBS_BLOCK, 6) void k_obs_eam(md_batch b, md_eam p, 
           min_image(D, pi, make_double4(q.x, q.y, q.z, 0.0), d);
           const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
           if (!(r2 < rc2)) return;
+          // atoms at one place: their densities and energies are finite (1e-150 for 0), their own
+          // virials have no value
           double ir;
-          const double r = sqrt_nr(r2, ir);
+          const double r = sqrt_nr(PASS == 0 ? fmax(r2, 1e-300) : r2, ir);
           double2 c[4];
           const double t = obs_interval(G, s_c, r, c, oor);
           const double v = 1.0 - t, t2 = t * t;
